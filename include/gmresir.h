@@ -134,8 +134,11 @@ size_t gmresir_matrix_storage_bytes(int64_t n, int64_t nnz);
 /* Build a handle.  rowptr/colidx/vals: device CSR arrays, borrowed (they
    must stay alive and unchanged while the handle is used).  storage: device
    buffer of gmresir_matrix_storage_bytes(n, nnz) bytes, 256-byte aligned,
-   owned by the caller and written here.  The row pointers are copied to the
-   host once to cut the rows into tiles of at most 512 rows / 2560 nonzeros.
+   owned by the caller and written here (also where an error is returned).
+   Kernels on the stream cut the rows into tiles of at most 512 rows / 2560
+   nonzeros and build the copies; the host reads back one small record.  (Only
+   a matrix with a row of more than 320 nonzeros has its row pointers copied to
+   the host, to cut its tiles there.)
    When no row has more than 512 nonzeros and the padding stays bounded, a
    sliced ELLPACK copy (slices of 64 rows, one row per lane) is built too.
    When the rows of every slice share their column offsets c - r (stencils:
@@ -145,9 +148,9 @@ size_t gmresir_matrix_storage_bytes(int64_t n, int64_t nnz);
    SpMV reads only the values (4 bytes per fp32 slot, no row lengths).
    Otherwise its column indices are 16-bit offsets from the row when every
    entry lies within 32767 columns of its row (the SpMV then reads 6 bytes per
-   fp32 nonzero instead of 8), else 32-bit indices.  colidx is copied to the
-   host (in windows of at most 16 MB) to build the offset lists.  Errors: INVALID_ARG (null pointer, n < 1, nnz < 0, nnz >= 2^31, rowptr not
-   monotone or rowptr[n] != nnz), WORKSPACE (storage too small), HIP. */
+   fp32 nonzero instead of 8), else 32-bit indices.  Errors: INVALID_ARG (null
+   pointer, n < 1, nnz < 0, nnz >= 2^31, rowptr not monotone or rowptr[n] !=
+   nnz), WORKSPACE (storage too small), HIP. */
 int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
                           const double* vals, void* storage, size_t storage_bytes, void* stream,
                           gmresir_matrix** out_host);

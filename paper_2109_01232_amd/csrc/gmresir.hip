@@ -14,7 +14,6 @@
 
 #include <algorithm>
 #include <chrono>
-#include <iterator>
 #include <map>
 #include <tuple>
 #include <mutex>
@@ -24,6 +23,7 @@
 #include "gmresir.h"
 #include "kernels.hpp"
 #include "lowsync.hpp"
+#include "setup.hpp"
 
 using namespace gir;
 
@@ -1377,6 +1377,40 @@ void add_result(gmresir_result* acc, const gmresir_result& r) {
 
 }  // namespace
 
+namespace {
+
+// The row tiles of a matrix with rows longer than TILE_MAX_ROW, cut greedily
+// on the host: <= TILE_ROWS rows and <= TILE_NNZ nonzeros, or one longer row.
+int cut_tiles(int64_t n, const int32_t* rowptr, int32_t* tile_row, hipStream_t s, int32_t* ntiles, int32_t* lds_nnz) {
+  std::vector<int32_t> rp(n + 1), tiles;
+  HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  tiles.push_back(0);
+  int64_t r0 = 0;
+  while (r0 < n) {
+    int64_t r = r0;
+    while (r < n && r - r0 < TILE_ROWS && (int64_t)rp[r + 1] - rp[r0] <= TILE_NNZ) ++r;
+    if (r == r0) {
+      r = r0 + 1;  // one row longer than a tile
+    } else if (r < n && (r & 7) && (r & ~(int64_t)7) > r0) {
+      r &= ~(int64_t)7;  // end tiles on a multiple of 8 rows (16-byte loads of 4 fp32 / 8 bf16 basis rows)
+    }
+    tiles.push_back((int32_t)r);
+    r0 = r;
+  }
+  *ntiles = (int32_t)tiles.size() - 1;
+  *lds_nnz = 1;
+  for (int t = 0; t < *ntiles; ++t) {
+    const int len = rp[tiles[t + 1]] - rp[tiles[t]];
+    if (len <= TILE_NNZ) *lds_nnz = std::max(*lds_nnz, len);
+  }
+  HIP_TRY(hipMemcpyAsync(tile_row, tiles.data(), tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  return GMRESIR_OK;
+}
+
+}  // namespace
+
 // ---------------------------------------------------------------------------
 // scratch memory of gmresir_solve_noalloc: a file-scope device array; every
 // GPU the library runs on holds its own copy until the process ends.  Host
@@ -1460,166 +1494,80 @@ int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const i
   }
   if (!ws_ok(storage, storage_bytes, need)) return GMRESIR_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  std::vector<int32_t> rp(n + 1);
-  HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  // storage regions, and inside the tile table's the scratch of the set-up kernels
+  const size_t E = (size_t)sell_max_entries(n, nnz);
+  const int64_t ns = (n + SELL_C - 1) / SELL_C;
+  const size_t tile_bytes = align_up((size_t)(max_tiles(n, nnz) + 1) * 4);
+  char* st = (char*)storage;
+  Setup S{};
+  S.n = (int)n;
+  S.nnz = nnz;
+  S.rowptr = rowptr;
+  S.col = colidx;
+  S.vals = vals;
+  S.ns = (int)ns;
+  S.nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(SETUP_MAX_BLOCKS, ns / SETUP_MIN_SLICES));
+  S.nseg = (int)((n + (int64_t)TILE_SEG * TILE_UNIT - 1) / ((int64_t)TILE_SEG * TILE_UNIT));
+  // a wave stages a slice with up to one entry a row more than the average
+  S.cap = (int)std::max<int64_t>(256, std::min<int64_t>(2048, SELL_C * (nnz / n + 2)));
+  S.max_entries = (long long)E;
+  S.v32 = (float*)st;
+  char* tbase = st + align_up((size_t)nnz * 4);
+  S.tile_row = (int*)tbase;
+  char* tend = tbase + tile_bytes;
+  S.dec = (SetupDecision*)(tend - sizeof(SetupDecision));
+  S.info = (SetupInfo*)((char*)S.dec - (size_t)S.nblocks * sizeof(SetupInfo));
+  S.entry = (int2*)((char*)S.info - (size_t)S.nseg * sizeof(int2));
+  S.chain = (int*)((char*)S.entry - (S.nseg > 1 ? (size_t)S.nseg * TILE_SPAN * sizeof(int) : 0));
+  if ((char*)S.chain < tbase + ((size_t)n / TILE_UNIT + 2) * sizeof(int32_t)) {
+    set_error("internal: set-up scratch does not fit");
+    return GMRESIR_ERR_INVALID_ARG;
+  }
+  S.sptr = (int*)tend;
+  S.scol = (int*)(tend + align_up((ns + 1) * 4));
+  S.sv32 = (float*)((char*)S.scol + align_up(E * 4));
+  S.sv64 = (double*)((char*)S.sv32 + align_up(E * 4));
+  const size_t seg_lds = (size_t)(TILE_SEG + TILE_SPAN + 1) * sizeof(int);
+  const size_t scan_lds = std::max(seg_lds, (size_t)NWAVES * S.cap * sizeof(int));
+  const size_t build_lds = std::max(seg_lds, (size_t)NWAVES * S.cap * (sizeof(int) + sizeof(double)));
+  hipLaunchKernelGGL(k_setup_scan, dim3(S.nblocks + (S.nseg > 1 ? S.nseg : 0)), dim3(BLOCK), scan_lds, s, S);
+  hipLaunchKernelGGL(k_setup_decide, dim3(1), dim3(SETUP_MAX_BLOCKS), 0, s, S);
+  hipLaunchKernelGGL(k_setup_build, dim3(S.nblocks + S.nseg), dim3(BLOCK), build_lds, s, S);
+  HIP_TRY(hipGetLastError());
+  SetupDecision dec;
+  HIP_TRY(hipMemcpyAsync(&dec, S.dec, sizeof(dec), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  if (rp[0] != 0 || rp[n] != nnz) {
+  if (dec.first != 0 || dec.last != nnz) {
     set_error("gmresir_matrix_create: rowptr[0] must be 0 and rowptr[n] == nnz");
     return GMRESIR_ERR_INVALID_ARG;
   }
-  for (int64_t i = 0; i < n; ++i)
-    if (rp[i + 1] < rp[i]) {
-      set_error("gmresir_matrix_create: rowptr decreases at row %lld", (long long)i);
-      return GMRESIR_ERR_INVALID_ARG;
-    }
-  // greedy cut into tiles of <= TILE_ROWS rows and <= TILE_NNZ nonzeros
-  std::vector<int32_t> tiles;
-  tiles.push_back(0);
-  int64_t r0 = 0;
-  while (r0 < n) {
-    int64_t r = r0;
-    while (r < n && r - r0 < TILE_ROWS && (int64_t)rp[r + 1] - rp[r0] <= TILE_NNZ) ++r;
-    if (r == r0) {
-      r = r0 + 1;  // one row longer than a tile
-    } else if (r < n && (r & 7) && (r & ~(int64_t)7) > r0) {
-      r &= ~(int64_t)7;  // end tiles on a multiple of 8 rows (16-byte loads of 4 fp32 / 8 bf16 basis rows)
-    }
-    tiles.push_back((int32_t)r);
-    r0 = r;
-  }
-  const int ntiles = (int)tiles.size() - 1;
-  int lds_nnz = 1;
-  for (int t = 0; t < ntiles; ++t) {
-    const int len = rp[tiles[t + 1]] - rp[tiles[t]];
-    if (len <= TILE_NNZ) lds_nnz = std::max(lds_nnz, len);
-  }
-  if (ntiles > max_tiles(n, nnz)) {
-    set_error("internal: tile bound exceeded");
+  if (dec.bad_row != INT32_MAX) {
+    set_error("gmresir_matrix_create: rowptr decreases at row %d", dec.bad_row);
     return GMRESIR_ERR_INVALID_ARG;
   }
-  char* st = (char*)storage;
-  float* v32 = (float*)st;
-  int32_t* tr = (int32_t*)(st + align_up((size_t)nnz * 4));
-  HIP_TRY(hipMemcpyAsync(tr, tiles.data(), tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  if (nnz > 0) {
-    int g = (int)std::min<int64_t>(4096, (nnz + BLOCK - 1) / BLOCK);
-    hipLaunchKernelGGL(k_cast_vals, dim3(g), dim3(BLOCK), 0, s, nnz, vals, v32);
-    HIP_TRY(hipGetLastError());
+  if (dec.max_len > TILE_MAX_ROW) {
+    // a row so long that tiles need not start on multiples of 8 rows
+    if (int e = cut_tiles(n, rowptr, S.tile_row, s, &dec.ntiles, &dec.lds_nnz)) return e;
   }
-  // sliced ELLPACK copy, if compact
-  const int64_t ns = (n + SELL_C - 1) / SELL_C;
-  std::vector<int32_t> sptr(ns + 1, 0);
-  bool sell = nnz > 0;
-  for (int64_t sl = 0; sl < ns && sell; ++sl) {
-    int64_t K = 0;
-    for (int64_t r = sl * SELL_C; r < std::min<int64_t>(n, (sl + 1) * SELL_C); ++r) K = std::max<int64_t>(K, rp[r + 1] - rp[r]);
-    if (K > SELL_MAX_ROW) sell = false;
-    const int64_t next = (int64_t)sptr[sl] + SELL_C * K;
-    if (next > sell_max_entries(n, nnz)) sell = false;
-    else sptr[sl + 1] = (int32_t)next;
-  }
-  const size_t E = (size_t)sell_max_entries(n, nnz);
-  // shared offsets: per slice the sorted union of its rows' offsets c - r,
-  // taken when every row's columns strictly increase and the slots grow by
-  // at most SHARED_MAX_GROWTH over the per-row copy (rows mostly repeat the
-  // previous row's offsets, so the union is merged only on a change)
-  bool shared = false;
-  std::vector<int32_t> sptr3, soff;
-  if (sell) {
-    // the column indices come to the host in windows of at most SHARED_SCAN_WINDOW
-    // entries, 16 MB (a slice's entries, <= 64 * SELL_MAX_ROW, always fit one
-    // window; the 27-point 128^3 matrix takes 14 windows)
-    constexpr int64_t SHARED_SCAN_WINDOW = (int64_t)1 << 22;
-    std::vector<int32_t> ci;
-    int64_t w0 = 0, w1 = 0;  // entries [w0, w1) held in ci
-    sptr3.assign(ns + 1, 0);
-    std::vector<int32_t> U, row, prev, merged;
-    bool ok = true;
-    for (int64_t sl = 0; sl < ns && ok; ++sl) {
-      const int64_t ra = sl * SELL_C, rb = std::min<int64_t>(n, (sl + 1) * SELL_C);
-      if (rp[rb] > w1) {
-        w0 = rp[ra];
-        w1 = std::min<int64_t>(nnz, std::max<int64_t>(w0 + SHARED_SCAN_WINDOW, rp[rb]));
-        ci.resize(w1 - w0);
-        HIP_TRY(hipMemcpyAsync(ci.data(), colidx + w0, (w1 - w0) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-      }
-      U.clear();
-      prev.clear();
-      for (int64_t r = ra; r < rb && ok; ++r) {
-        row.clear();
-        for (int64_t p = rp[r]; p < rp[r + 1]; ++p) {
-          const int32_t d = ci[p - w0] - (int32_t)r;
-          if (!row.empty() && d <= row.back()) {
-            ok = false;
-            break;
-          }
-          row.push_back(d);
-        }
-        if (!ok || row == prev) continue;
-        merged.clear();
-        std::set_union(U.begin(), U.end(), row.begin(), row.end(), std::back_inserter(merged));
-        U.swap(merged);
-        prev = row;
-      }
-      if ((int64_t)U.size() > SELL_MAX_ROW) ok = false;
-      if (!ok) break;
-      soff.insert(soff.end(), U.begin(), U.end());
-      sptr3[sl + 1] = sptr3[sl] + SELL_C * (int32_t)U.size();
-    }
-    shared = ok && (size_t)sptr3[ns] <= E && (double)sptr3[ns] <= SHARED_MAX_GROWTH * (double)sptr[ns];
-  }
-  bool wide = false;
-  if (shared)
-    for (int64_t sl = 0; sl < ns && !wide; ++sl) wide = sptr3[sl + 1] - sptr3[sl] > 9 * SELL_C;
-  char* sbase = st + align_up((size_t)nnz * 4) + align_up((size_t)(max_tiles(n, nnz) + 1) * 4);
-  int32_t* d_sptr = (int32_t*)sbase;
-  int32_t* d_scol = (int32_t*)(sbase + align_up((ns + 1) * 4));
-  float* d_sv32 = (float*)((char*)d_scol + align_up(E * 4));
-  double* d_sv64 = (double*)((char*)d_sv32 + align_up(E * 4));
-  bool d16 = false;
-  if (shared) {
-    HIP_TRY(hipMemcpyAsync(d_sptr, sptr3.data(), (ns + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(d_scol, soff.data(), soff.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_build_sell_shared, dim3((unsigned)ns), dim3(SELL_C), 0, s, (int)n, rowptr, colidx, vals,
-                       d_sptr, d_scol, d_sv32, d_sv64);
-    HIP_TRY(hipGetLastError());
-  } else if (sell) {
-    // 16-bit column offsets if every entry is within 32767 columns of its row
-    // (the check's flag sits in the column region until the copy is built)
-    int far = 1;
-    HIP_TRY(hipMemsetAsync(d_scol, 0, sizeof(int), s));
-    const int gc = (int)std::min<int64_t>(4096, (n + BLOCK - 1) / BLOCK);
-    hipLaunchKernelGGL(k_col_offset_check, dim3(gc), dim3(BLOCK), 0, s, (int)n, rowptr, colidx, (int*)d_scol);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(&far, d_scol, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    d16 = far == 0;
-    HIP_TRY(hipMemcpyAsync(d_sptr, sptr.data(), (ns + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_build_sell, dim3((unsigned)ns), dim3(SELL_C), 0, s, (int)n, rowptr, colidx, vals, d_sptr,
-                       d_scol, (short*)d_scol, d16 ? 1 : 0, d_sv32, d_sv64);
-    HIP_TRY(hipGetLastError());
-  }
-  HIP_TRY(hipStreamSynchronize(s));
   gmresir_matrix* A = new gmresir_matrix;
-  A->sell = sell;
+  A->sell = dec.sell != 0;
   A->nslices = (int)ns;
-  A->sell_ptr = d_sptr;
-  A->sell_col = d_scol;
-  A->sell_d16 = d16;
-  A->sell_shared = shared;
-  A->sell_wide = wide;
-  A->sell_v32 = d_sv32;
-  A->sell_v64 = d_sv64;
+  A->sell_ptr = S.sptr;
+  A->sell_col = S.scol;
+  A->sell_d16 = dec.d16 != 0;
+  A->sell_shared = dec.shared != 0;
+  A->sell_wide = dec.wide != 0;
+  A->sell_v32 = S.sv32;
+  A->sell_v64 = S.sv64;
   A->n = n;
   A->nnz = nnz;
   A->rowptr = rowptr;
   A->colidx = colidx;
   A->vals64 = vals;
-  A->vals32 = v32;
-  A->tile_row = tr;
-  A->ntiles = ntiles;
-  A->lds_nnz = lds_nnz;
+  A->vals32 = S.v32;
+  A->tile_row = S.tile_row;
+  A->ntiles = dec.ntiles;
+  A->lds_nnz = dec.lds_nnz;
   A->device = 0;
   (void)hipGetDevice(&A->device);
   *out = A;

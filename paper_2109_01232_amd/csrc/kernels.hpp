@@ -1697,81 +1697,6 @@ __global__ __launch_bounds__(BLOCK) void k_spmv(Csr A, const T* __restrict__ x, 
   else spmv_tiles<T>(A, XPlain<T>{x}, epi, prod, s_scr);
 }
 
-__global__ void k_cast_vals(int64_t nnz, const double* __restrict__ v64, float* __restrict__ v32) {
-  for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * BLOCK)
-    v32[i] = (float)v64[i];
-}
-
-// *flag != 0 if some entry lies more than 32767 columns from its row (then
-// the sliced copy keeps 32-bit columns).  Grid-stride over the rows.
-__global__ void k_col_offset_check(int n, const int* __restrict__ rowptr, const int* __restrict__ colidx, int* flag) {
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < n; r += gridDim.x * blockDim.x) {
-    bool far = false;
-    for (int p = rowptr[r]; p < rowptr[r + 1]; ++p) {
-      const int d = colidx[p] - r;
-      far = far || d > 32767 || d < -32767;
-    }
-    if (far) atomicOr(flag, 1);
-  }
-}
-
-// Fill the sliced ELLPACK copy (one block of 64 threads per slice, one row per
-// thread); fp32 values rounded to nearest even like the CSR copy.  Columns are
-// stored as 32-bit indices, or (d16) as 16-bit offsets from the row, which
-// take a quarter of the SpMV's bytes off (6 instead of 8 per fp32 nonzero).
-// Padding entries point at the row itself (offset 0), rows past n at row 0.
-__global__ void k_build_sell(int n, const int* __restrict__ rowptr, const int* __restrict__ colidx,
-                             const double* __restrict__ vals, const int* __restrict__ sptr, int* __restrict__ scol,
-                             short* __restrict__ scol16, int d16, float* __restrict__ sv32,
-                             double* __restrict__ sv64) {
-  const int sl = blockIdx.x, lane = threadIdx.x;
-  const int r = sl * SELL_C + lane;
-  const int base = sptr[sl];
-  const int K = (sptr[sl + 1] - base) / SELL_C;
-  const int p0 = r < n ? rowptr[r] : 0;
-  const int len = r < n ? rowptr[r + 1] - p0 : 0;
-  const int rr = r < n ? r : 0;
-  for (int k = 0; k < K; ++k) {
-    const int e = base + SELL_C * k + lane;
-    int c = rr;
-    double v = 0.0;
-    if (k < len) {
-      c = colidx[p0 + k];
-      v = vals[p0 + k];
-    }
-    if (d16) scol16[e] = (short)(c - rr);
-    else scol[e] = c;
-    sv64[e] = v;
-    sv32[e] = (float)v;
-  }
-}
-
-// Values of the shared-offset sliced copy (one block of 64 threads per
-// slice, one row per thread): slot k of the row takes the CSR entry at column
-// r + soff[k] if the row has one, else 0; fp32 values rounded to nearest even
-// like the CSR copy.  The host has checked that every row's columns strictly
-// increase and lie in its slice's offset list, so one pass with a cursor
-// takes every entry.
-__global__ void k_build_sell_shared(int n, const int* __restrict__ rowptr, const int* __restrict__ colidx,
-                                    const double* __restrict__ vals, const int* __restrict__ sptr,
-                                    const int* __restrict__ soff_all, float* __restrict__ sv32,
-                                    double* __restrict__ sv64) {
-  const int sl = blockIdx.x, lane = threadIdx.x;
-  const int r = sl * SELL_C + lane;
-  const int base = sptr[sl];
-  const int K = (sptr[sl + 1] - base) / SELL_C;
-  const int* soff = soff_all + base / SELL_C;
-  int p = r < n ? rowptr[r] : 0;
-  const int pe = r < n ? rowptr[r + 1] : 0;
-  for (int k = 0; k < K; ++k) {
-    double v = 0.0;
-    if (p < pe && colidx[p] - r == soff[k]) v = vals[p++];
-    const int e = base + SELL_C * k + lane;
-    sv64[e] = v;
-    sv32[e] = (float)v;
-  }
-}
-
 // v[i] = 2 * (splitmix64(seed ^ i) >> 11) * 2^-53 - 1 (SplitMix64, S. Vigna).
 __global__ void k_start_vector(int n, uint64_t seed, double* __restrict__ v) {
   for (int i = blockIdx.x * BLOCK + threadIdx.x; i < n; i += gridDim.x * BLOCK) {
