@@ -16,8 +16,9 @@
  *    parameter name ends in _host.  The library never calls hipMalloc or
  *    hipFree: every device buffer holding data is passed in.  (Host-side
  *    handles are allocated with malloc/new; gmresir_solve on systems of at
- *    most 2^18 rows records its inner cycle as a HIP graph, and profiling
- *    creates HIP events -- runtime objects the HIP runtime backs itself.)
+ *    most 2^18 rows launches its inner cycle cooperatively or records it as a
+ *    HIP graph, and profiling creates HIP events -- runtime objects the HIP
+ *    runtime backs itself.)
  *  - Work is enqueued on the caller's `stream` (a hipStream_t passed as
  *    void*; NULL is the legacy default stream).  Functions that return host
  *    values synchronise that stream before returning.
@@ -184,10 +185,16 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    hist_host (may be NULL): receives up to hist_cap per-iteration values
    |g_{j+1}| / |g_1|, the implicit residual of each inner iteration relative
    to the right-hand side of its cycle.  The stream is synchronised once per
-   refinement.  b = 0 gives x = 0 and GMRESIR_OK.  For n <= 2^18 (and
-   profile = 0) the kernels of one inner cycle are recorded once as a HIP
-   graph and replayed for every later cycle of the same length (the same
-   kernels and bits as direct launches; less host launch work). */
+   refinement.  b = 0 gives x = 0 and GMRESIR_OK.
+   How a cycle is launched (profile = 0) depends on the system's size.  Where
+   the basis fits the registers of the GPU's compute units (layout 3, no
+   preconditioner, ortho 0, restart <= 112; up to 262144 rows in fp32 and
+   131072 in fp64 at restart 50) it is one cooperative kernel, whose blocks
+   wait for each other inside it; HIP errors when one of them does not answer
+   for a minute.  Other systems of n <= 2^18 record the kernels of a cycle once
+   as a HIP graph, replayed for every later cycle of the same length.  With
+   profile = 1 and in gmresir_solve_noalloc every kernel is launched directly;
+   the bits are the same. */
 int gmresir_solve(const gmresir_matrix* A, const double* b, double* x, const gmresir_params* p,
                   const double* poly_roots_host, void* ws, size_t ws_bytes, gmresir_result* res_host,
                   double* hist_host, int64_t hist_cap, void* stream);

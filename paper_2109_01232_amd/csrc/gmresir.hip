@@ -24,6 +24,7 @@
 #include "kernels.hpp"
 #include "lowsync.hpp"
 #include "setup.hpp"
+#include "small.hpp"
 
 using namespace gir;
 
@@ -990,7 +991,7 @@ struct Ctx {
   ~Ctx() { drop_graph(); }
 
   void run_cycle(int kmax) {
-    if (!graph_ok) {
+    if (!graph_ok || small_R > 0) {
       cycle(kmax);
       return;
     }
@@ -1021,8 +1022,93 @@ struct Ctx {
     prof->pend.insert(prof->pend.end(), graph_entries.begin(), graph_entries.end());
   }
 
+  // -------------------------------------------------------------------------
+  // systems whose basis fits the compute units' LDS: the cycle as one
+  // cooperative launch, or its phases one by one (small.hpp)
+  // -------------------------------------------------------------------------
+
+  int small_R = 0, small_P = 0;  // rows per block, blocks (0: not this path)
+  bool small_coop = false;
+  unsigned int small_tag = 2;
+
+  unsigned long long* words() const { return (unsigned long long*)((char*)part + SMALL_WORDS_AT); }
+
+  // called once the solve's options are known, before its first cycle
+  void small_init(bool coop) {
+    if (!A->sell_shared || L.bj > 0 || L.ls || poly_on) return;
+    small_R = small_rows(n, L.m, (int)sizeof(T), device_cus(A->device));
+    if (small_R == 0) return;
+    small_P = (n + small_R - 1) / small_R;
+    small_coop = coop && !prof->on;
+    small_clear(words(), small_words(small_P, (int)sizeof(T)), stream);
+    // the vector as words lies in w1 and w2 (adjacent; used by the phases only)
+    if (small_coop) small_clear((unsigned long long*)w1, (size_t)L.ldv * sizeof(T) * 2 / 8, stream);
+  }
+
+  SmallArgs<T, S> small_args(int j, int kmax) const {
+    SmallArgs<T, S> a{};
+    a.A = Ain;
+    a.wtmp = wtmp;
+    a.w1 = w1;
+    a.w2 = w2;
+    a.V = V;
+    a.ldv = L.ldv;
+    a.st = st;
+    a.words = words();
+    a.x = (unsigned long long*)w1;
+    a.tag = small_tag;
+    a.vals_lds = (unsigned)small_cycle_lds(small_R, (int)sizeof(T));
+    a.rows = small_R;
+    a.blocks = small_P;
+    a.j = j;
+    a.kmax = kmax;
+    return a;
+  }
+
+  // phase ph of iteration j: launched, or only booked (the cycle kernel runs it)
+  void small_phase(SmallPhase ph, int j, int kmax, bool launch) {
+    const int cat = ph == SMALL_SPMV     ? GMRESIR_CAT_SPMV_PROJ
+                    : ph == SMALL_UPDATE ? GMRESIR_CAT_UPDATE_PROJ
+                    : ph == SMALL_NORM   ? GMRESIR_CAT_UPDATE_NORM
+                                         : GMRESIR_CAT_TAIL;
+    const double b = ph == SMALL_GIVENS ? 0.0
+                     : ph == SMALL_SPMV ? spmv_bytes() + sT() * n * 2 + sS() * n * (j + 1)
+                                        : sT() * n * 2 + sS() * n * (j + 1);
+    prof->tag = j;
+    prof->early = false;
+    if (!launch) {
+      prof->pend.push_back({cat, b, j, false, nullptr, nullptr});
+      return;
+    }
+    const int g = ph == SMALL_GIVENS ? 1 : small_P;
+    prof->launch(cat, b, small_kernel<T, S>(ph, L.m, small_R), dim3(g), dim3(SMALL_NT),
+                 small_phase_lds(small_R, (int)sizeof(T)), stream, small_args(j, kmax));
+  }
+
+  void small_cycle(int kmax) {
+    bool launched = false;
+    if (small_coop) {
+      SmallArgs<T, S> a = small_args(0, kmax);
+      void* args[] = {&a};
+      launched = hipLaunchCooperativeKernel((const void*)small_kernel<T, S>(SMALL_CYCLE, L.m, small_R), dim3(small_P),
+                                            dim3(SMALL_NT), args, a.vals_lds, stream) == hipSuccess;
+      if (!launched) {
+        (void)hipGetLastError();
+        small_coop = false;
+      }
+    }
+    for (int j = 0; j < kmax; ++j)
+      for (SmallPhase ph : {SMALL_SPMV, SMALL_UPDATE, SMALL_NORM, SMALL_GIVENS}) small_phase(ph, j, kmax, !launched);
+    prof->tag = -1;
+    small_tag += SMALL_MAX_M + 2;
+  }
+
   // the Arnoldi steps of one cycle, ending with its last Givens step
   void cycle(int kmax) {
+    if (small_R > 0) {
+      small_cycle(kmax);
+      return;
+    }
     if constexpr (sizeof(S) == sizeof(T)) {
       if (L.ls) {  // (the parameter check keeps bf16 bases off this path)
         ls_cycle(kmax);
@@ -1122,6 +1208,10 @@ struct Ctx {
     HIP_TRY(hipStreamSynchronize(stream));
     HIP_TRY(hipGetLastError());
     prof->commit(h->cycle_k);
+    if (h->lost) {
+      set_error("the blocks of a cycle kernel did not all answer within its time limit");
+      return GMRESIR_ERR_HIP;
+    }
     return 0;
   }
 };
@@ -1159,6 +1249,7 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
     return GMRESIR_ERR_INVALID_ARG;
   }
   c.init(p->rtol, p->check_mode, 0.0);
+  c.small_init(allow_graph);
   if (L.bj > 0) c.bj_setup();
   c.norm64(b, &c.st.hdr->beta);
   c.resid64(x, b);
@@ -1303,6 +1394,7 @@ int arnoldi32(const gmresir_matrix* A, const double* src, int steps, char* ws, c
   prof.stream = stream;
   Ctx<float, float> c(A, ws, L, stream, &prof);
   c.init(0.0, 0, 1.0);
+  c.small_init(true);
   c.cast(src);
   c.cycle(steps);
   // the Hessenberg matrix and the history are copied on the stream before

@@ -1,0 +1,74 @@
+// Inner cycles of systems whose Krylov basis fits the LDS of the GPU's
+// compute units (declarations; kernels in small.hip).
+//
+// A cycle of such a system is bound by latency: as separate kernels an
+// iteration is five dependent launches of a few microseconds each whatever the
+// rows.  Here the rows are split over at most one block per compute unit, each
+// block keeps its rows of V in LDS, and one cooperative launch runs the whole
+// cycle.  The three reductions of an iteration (h1, h2, ||w''||^2) are
+// exchanges between the blocks: a block stores its partial sums as 64-bit
+// words of value and tag, and every block reads and sums all of them in the
+// same order.  A word is complete when its tag is the iteration's, so an
+// exchange is one store and one load in flight, without flags, fences or a
+// second trip.
+//
+// The same phases can be launched one by one (profiling, the allocation-free
+// entry point, or when a cooperative launch is refused): the same partition,
+// order of operations and words, so the same bits.
+#pragma once
+
+#include "device.hpp"
+
+namespace gir {
+
+// Waves of a block: seven share the columns (wave w has c = w + 7 q), one makes
+// the Givens steps; with eight a lane has 256 registers (with a ninth 168).
+constexpr int SMALL_NW = 7;
+constexpr int SMALL_NT = (SMALL_NW + 1) * WAVE;
+constexpr int SMALL_MAX_M = 16 * SMALL_NW;           // restart lengths of this path
+constexpr int SMALL_MAX_RL = 16;                     // rows per lane (64 RL rows per block)
+constexpr size_t SMALL_LDS = 160 << 10;              // of a compute unit
+constexpr int SMALL_MAX_P = 256;                     // blocks
+constexpr size_t SMALL_WORDS_AT = (size_t)MAX_BLOCKS * 8;  // the words follow the partials of the cycle's set-up
+
+enum SmallPhase { SMALL_SPMV = 0, SMALL_GIVENS, SMALL_UPDATE, SMALL_NORM, SMALL_CYCLE };
+
+template <typename T, typename S>
+struct SmallArgs {
+  Csr A;
+  T* wtmp;  // unnormalised next basis vector
+  T* w1;    // phases launched one by one: A v_j and w'
+  T* w2;
+  S* V;
+  long ldv;
+  State st;
+  unsigned long long* words;  // partial sums: h1, h2 (a line per wave and block), norm (a line per block)
+  unsigned long long* x;      // the unnormalised vector as words (the cycle kernel's gathers)
+  unsigned int tag;           // of the cycle, > 1; iteration j uses tag + j, the gathers of j = 0 tag - 1
+  unsigned int vals_lds;  // dynamic LDS of the cycle kernel: the block's rows of A, if they fit
+  int rows, blocks;           // partition: rows per block (multiple of 64), blocks
+  int j, kmax;
+};
+
+template <typename T>
+constexpr int small_words_per_value() {
+  return sizeof(T) / 4;
+}
+
+// Rows per block of an n-row system at restart m, or 0 if it does not fit.
+int small_rows(int64_t n, int m, int sT, int cus);
+size_t small_cycle_lds(int rows, int sT);  // dynamic LDS: of the cycle kernel, of a phase
+size_t small_phase_lds(int rows, int sT);
+
+template <typename T, typename S>
+using SmallKernel = void (*)(SmallArgs<T, S>);
+template <typename T, typename S>
+SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows);
+
+// words of the partial sums
+size_t small_words(int blocks, int sT);
+
+// sets every word's tag to 0 (never an iteration's)
+void small_clear(unsigned long long* words, size_t count, hipStream_t s);
+
+}  // namespace gir
