@@ -191,10 +191,14 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    preconditioner, ortho 0, restart <= 112; up to 262144 rows in fp32 and
    131072 in fp64 at restart 50) it is one cooperative kernel, whose blocks
    wait for each other inside it; HIP errors when one of them does not answer
-   for a minute.  Other systems of n <= 2^18 record the kernels of a cycle once
-   as a HIP graph, replayed for every later cycle of the same length.  With
-   profile = 1 and in gmresir_solve_noalloc every kernel is launched directly;
-   the bits are the same. */
+   for a minute.  So it is, with only the first columns of the basis in
+   registers, for larger systems of such matrices up to 2^21 rows (2^20 in
+   fp64) at restart <= 64, if the rows of x that a 256th of the rows reach fit
+   a compute unit's LDS.  Other systems of n <= 2^18 record the kernels of a
+   cycle once as a HIP graph, replayed for every later cycle of the same
+   length.  With profile = 1 and in gmresir_solve_noalloc every kernel is
+   launched directly; the bits are the same, but for the larger systems: their
+   cycle kernel sums in another order. */
 int gmresir_solve(const gmresir_matrix* A, const double* b, double* x, const gmresir_params* p,
                   const double* poly_roots_host, void* ws, size_t ws_bytes, gmresir_result* res_host,
                   double* hist_host, int64_t hist_cap, void* stream);

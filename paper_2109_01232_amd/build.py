@@ -21,7 +21,7 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libgmresir.so")
 
 ARCH = os.environ.get("GMRESIR_OFFLOAD_ARCH", "gfx950")
-HIP_SOURCES = ["gmresir.hip", "small.hip", "mlp.hip"]
+HIP_SOURCES = ["gmresir.hip", "small.hip", "mid.hip", "mlp.hip"]
 CXX_SOURCES = ["host_linalg.cpp", "errors.cpp"]
 
 

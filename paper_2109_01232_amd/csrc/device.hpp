@@ -95,7 +95,8 @@ struct StateHdr {
   int32_t cycle_k;      // k and flags of the last finished cycle (kept across
   int32_t cycle_flags;  // the reset a new cycle start does)
   int32_t lost;         // an exchange between the blocks of a cycle kernel timed out
-  int32_t pad[2];
+  int32_t wide;         // a block's window of x does not fit the cycle kernel of mid.hip
+  int32_t pad;
   uint32_t spare[8];
 };
 

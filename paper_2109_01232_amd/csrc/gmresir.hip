@@ -54,6 +54,12 @@ struct gmresir_matrix {
 namespace {
 
 constexpr int MAX_GRID = 1024;  // <= MAX_BLOCKS (partials per reduction)
+// Systems of more rows run the cycle kernel of mid.hip where it takes them (up
+// to 2^21 rows, 2^20 in fp64): from a little past the limits of the one of
+// small.hip, the smallest sizes measured.  It is the faster one over all of
+// that range: solves of 263169 rows 88.5 -> 41.8 ms, 10^6 211 -> 149, 2^21 51.0
+// -> 44.9 (27-point, fp32); fp64 136900 rows 59.7 -> 34.7, 1030301 50.7 -> 40.0.
+int64_t mid_min_n(int m, int sT) { return (sT == 4 && m <= 56 ? 1 << 18 : 1 << 17) + 1024; }
 constexpr int64_t GRAPH_MAX_N = 1 << 18;  // cycles of smaller systems run as HIP graphs
 constexpr size_t ALIGN = 256;
 
@@ -991,7 +997,7 @@ struct Ctx {
   ~Ctx() { drop_graph(); }
 
   void run_cycle(int kmax) {
-    if (!graph_ok || small_R > 0) {
+    if (!graph_ok || small_R > 0 || mid_k.k) {
       cycle(kmax);
       return;
     }
@@ -1033,9 +1039,44 @@ struct Ctx {
 
   unsigned long long* words() const { return (unsigned long long*)((char*)part + SMALL_WORDS_AT); }
 
+  // larger systems: the cycle as one cooperative launch with part of the basis
+  // in registers (mid.hip); nullptr: not this path
+  MidKernel<T, S> mid_k{};
+
+  void mid_init() {
+    if (!A->sell_shared || L.bj > 0 || L.ls || poly_on || prof->on || L.m > MID_MAX_M ||
+        n <= mid_min_n(L.m, (int)sizeof(T)) || device_cus(A->device) < MID_BLOCKS)
+      return;
+    mid_k = mid_kernel<T, S>(A->nslices);
+    if (!mid_k.k) return;
+    small_clear(words(), mid_words(), stream);
+    mid_fits(Ain, mid_k.chunks, &st.hdr->wide, stream);  // read with the first residual
+  }
+
+  bool mid_cycle(int kmax) {
+    SmallArgs<T, S> a = small_args(0, kmax);
+    a.rows = mid_k.chunks;
+    void* args[] = {&a};
+    if (hipLaunchCooperativeKernel((const void*)mid_k.k, dim3(MID_BLOCKS), dim3(MID_THREADS), args, mid_k.lds,
+                                   stream) !=
+        hipSuccess) {
+      (void)hipGetLastError();
+      mid_k.k = nullptr;
+      return false;
+    }
+    // booked as the kernels whose work it does
+    for (int j = 0; j < kmax; ++j)
+      for (SmallPhase ph : {SMALL_SPMV, SMALL_GIVENS, SMALL_UPDATE, SMALL_GIVENS, SMALL_NORM})
+        small_phase(ph, j, kmax, false);
+    prof->tag = -1;
+    small_tag += SMALL_MAX_M + 2;
+    return true;
+  }
+
   // called once the solve's options are known, before its first cycle
-  void small_init(bool coop) {
-    if (!A->sell_shared || L.bj > 0 || L.ls || poly_on) return;
+  void small_init(bool coop, bool mid) {
+    if (mid) mid_init();
+    if (mid_k.k || !A->sell_shared || L.bj > 0 || L.ls || poly_on) return;
     small_R = small_rows(n, L.m, (int)sizeof(T), device_cus(A->device));
     if (small_R == 0) return;
     small_P = (n + small_R - 1) / small_R;
@@ -1105,6 +1146,7 @@ struct Ctx {
 
   // the Arnoldi steps of one cycle, ending with its last Givens step
   void cycle(int kmax) {
+    if (mid_k.k && mid_cycle(kmax)) return;
     if (small_R > 0) {
       small_cycle(kmax);
       return;
@@ -1249,13 +1291,14 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
     return GMRESIR_ERR_INVALID_ARG;
   }
   c.init(p->rtol, p->check_mode, 0.0);
-  c.small_init(allow_graph);
+  c.small_init(allow_graph, allow_graph);
   if (L.bj > 0) c.bj_setup();
   c.norm64(b, &c.st.hdr->beta);
   c.resid64(x, b);
   c.cast(c.r64);
   StateHdr H;
   if (int e = c.read_hdr(&H)) return e;
+  if (H.wide) c.mid_k.k = nullptr;
   const double beta = H.beta;
   double gamma = H.gamma;
   int status = GMRESIR_OK;
@@ -1394,7 +1437,7 @@ int arnoldi32(const gmresir_matrix* A, const double* src, int steps, char* ws, c
   prof.stream = stream;
   Ctx<float, float> c(A, ws, L, stream, &prof);
   c.init(0.0, 0, 1.0);
-  c.small_init(true);
+  c.small_init(true, false);
   c.cast(src);
   c.cycle(steps);
   // the Hessenberg matrix and the history are copied on the stream before

@@ -1060,6 +1060,7 @@ __global__ void k_init_state(State st, double rtol, int check_mode, double gamma
     hd->cycle_k = 0;
     hd->cycle_flags = 0;
     hd->lost = 0;
+    hd->wide = 0;
     for (int i = 0; i < 8; ++i) hd->spare[i] = 0u;
   }
 }

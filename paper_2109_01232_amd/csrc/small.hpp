@@ -71,4 +71,27 @@ size_t small_words(int blocks, int sT);
 // sets every word's tag to 0 (never an iteration's)
 void small_clear(unsigned long long* words, size_t count, hipStream_t s);
 
+// mid.hip: cycles of larger systems, the first columns of the basis in
+// registers; one block per compute unit (MID_BLOCKS of MID_THREADS threads),
+// or nullptr where the system is too large.  Uses SmallArgs' A, wtmp, V, ldv,
+// st, words, tag and kmax.
+constexpr int MID_BLOCKS = 256, MID_THREADS = 512, MID_MAX_M = 64;
+template <typename T, typename S>
+struct MidKernel {
+  SmallKernel<T, S> k;
+  int chunks;    // capacity of its window of x (SmallArgs' rows)
+  unsigned lds;  // dynamic LDS
+};
+// sets *wide if a block's window does not fit
+void mid_fits(const Csr& A, int chunks, int* wide, hipStream_t s);
+template <typename T, typename S>
+MidKernel<T, S> mid_kernel(int64_t nslices);
+template <>
+MidKernel<float, float> mid_kernel<float, float>(int64_t nslices);
+template <>
+MidKernel<float, bf16_t> mid_kernel<float, bf16_t>(int64_t nslices);
+template <>
+MidKernel<double, double> mid_kernel<double, double>(int64_t nslices);
+size_t mid_words();
+
 }  // namespace gir
