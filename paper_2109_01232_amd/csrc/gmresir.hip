@@ -1122,7 +1122,7 @@ struct Ctx {
       return;
     }
     const int g = ph == SMALL_GIVENS ? 1 : small_P;
-    prof->launch(cat, b, small_kernel<T, S>(ph, L.m, small_R), dim3(g), dim3(SMALL_NT),
+    prof->launch(cat, b, small_kernel<T, S>(ph, L.m, small_R, small_P), dim3(g), dim3(SMALL_NT),
                  small_phase_lds(small_R, (int)sizeof(T)), stream, small_args(j, kmax));
   }
 
@@ -1131,7 +1131,7 @@ struct Ctx {
     if (small_coop) {
       SmallArgs<T, S> a = small_args(0, kmax);
       void* args[] = {&a};
-      launched = hipLaunchCooperativeKernel((const void*)small_kernel<T, S>(SMALL_CYCLE, L.m, small_R), dim3(small_P),
+      launched = hipLaunchCooperativeKernel((const void*)small_kernel<T, S>(SMALL_CYCLE, L.m, small_R, small_P), dim3(small_P),
                                             dim3(SMALL_NT), args, a.vals_lds, stream) == hipSuccess;
       if (!launched) {
         (void)hipGetLastError();

@@ -17,13 +17,91 @@ namespace {
 // one line: 3.0 instead of 1.1 us per exchange of 16 blocks), and a reader
 // that looks too early takes the line from the writer: POLL_WAIT (times 64
 // clocks) after its own store it looks for the first time, about when the
-// others' stores have arrived (1.8 -> 1.1 us).
-constexpr int POLL_WAIT = 12;
+// others' stores have arrived (1.8 -> 1.1 us).  WAIT_ONE, WAIT_TWO: the same in
+// two stages, for the blocks that sum a group and for those that wait for them.
+constexpr int POLL_WAIT = 12, WAIT_ONE = 8, WAIT_TWO = 16;
 constexpr int LINE = 16;
 
 template <typename T>
 __device__ __forceinline__ word_t* line_of(word_t* words, int P, int wid, int b) {
-  return words + ((size_t)wid * P + b) * (LINE * small_words_per_value<T>());
+  return words + ((size_t)wid * (P + SMALL_GROUPS) + b) * (LINE * small_words_per_value<T>());
+}
+
+// Past 64 blocks the lines are summed in two stages, first those of up to 16
+// blocks of a die (block b runs on die b % 8) by one of them, which writes the
+// group's line behind the blocks' (1.8 us at 256 blocks, where reading every
+// line takes 5 us; 2.4 us at 128).
+__host__ __device__ constexpr bool small_staged(int P) { return P > WAVE; }
+constexpr int SMALL_STAGED_RL = 4;  // rows per lane from which on there are more than 64 blocks
+struct Group {
+  int g, first, count;  // its line, its first block (then every eighth), its blocks
+  __device__ __forceinline__ Group(int g_, int P)
+      : g(g_), first(g_ % 8 + 128 * (g_ / 8)), count(min(16, (P - first + 7) / 8)) {}
+};
+__device__ __forceinline__ int group_of(int b) { return b % 8 + 8 * (b / 128); }
+__device__ __forceinline__ bool leads_group(int b) { return b / 8 % 16 == 0; }
+__device__ __forceinline__ int groups_of(int P) { return 8 + max(0, min(8, P - 128)); }
+
+// out, lane l: the sum of value l % W over `count` <= 16 lines, `stride` words
+// apart; values from nq on are not there.  False on time-out.
+template <typename T, int W>
+__device__ __forceinline__ bool take(const word_t* lines, int stride, int count, int nq, unsigned int tag, int lane,
+                                     T& out) {
+  constexpr int WV = small_words_per_value<T>();
+  constexpr int NB = WAVE / W < 16 ? WAVE / W : 16, G = 16 / NB;
+  const int q = lane % W, bl = lane / W;
+  word_t w[G][WV];
+  const bool ok = poll([&] {
+    bool right = true;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int b = NB * g + bl;
+#pragma unroll
+      for (int h = 0; h < WV; ++h) w[g][h] = get_word(lines + (unsigned)((b < count ? b : 0) * stride + WV * q + h));
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int h = 0; h < WV; ++h)
+        right = right && ((unsigned int)w[g][h] == tag || q >= nq || NB * g + bl >= count);
+    return right;
+  });
+  if (!ok) return false;
+  T s = T(0);
+#pragma unroll
+  for (int g = 0; g < G; ++g) s += NB * g + bl < count && bl < NB && q < nq ? word_value(w[g], T(0)) : T(0);
+  out = lane_sum<W>(s);
+  return true;
+}
+
+// The two stages over P lines from `lines`, `line` words each, the groups'
+// behind them.  The cycle kernel's blocks share the first one; with `alone`
+// (single phases, every line is there) a wave does all of it in the same order.
+template <typename T, int W>
+__device__ __forceinline__ bool take_staged(word_t* lines, int line, int P, bool leader, bool alone, int nq,
+                                            unsigned int tag, int lane, T& out) {
+  constexpr int NB = WAVE / W < 16 ? WAVE / W : 16;
+  if (alone) {
+    T sum = T(0);
+    for (int g = 0; g < groups_of(P); ++g) {
+      const Group G(g, P);
+      T s;
+      if (!take<T, W>(lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
+      sum += lane / W == g % NB && lane % W < nq ? s : T(0);
+    }
+    out = lane_sum<W>(sum);
+    return true;
+  }
+  if (leader) {
+    const Group G(group_of(blockIdx.x), P);
+    T s;
+    if (!take<T, W>(lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
+    if (lane < nq) put_value(lines + (size_t)(P + G.g) * line + small_words_per_value<T>() * lane, s, tag);
+    __builtin_amdgcn_s_sleep(WAIT_ONE);
+  } else {
+    __builtin_amdgcn_s_sleep(WAIT_TWO);
+  }
+  return take<T, W>(lines + (size_t)P * line, line, groups_of(P), nq, tag, lane, out);
 }
 
 // the wave's sums of acc[q], q < nq: its columns' partial sums
@@ -39,39 +117,44 @@ __device__ __forceinline__ void publish(word_t* words, int P, int wid, int lane,
 // out[q], q < nq: the sums over the P blocks, in every lane, and kept in
 // all[wid + 7 q].  SLOTS lanes take a line's values side by side, 64 / SLOTS
 // blocks at once; a pass has up to eight such loads in flight.
-template <typename T, int SLOTS>
+template <typename T, int SLOTS, bool STAGED>
 __device__ __forceinline__ bool collect(word_t* words, int P, int wid, int lane, unsigned int tag, T (&out)[SLOTS],
-                                        T* all, int nq) {
+                                        T* all, int nq, bool alone = false) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int W = SLOTS, NB = WAVE / W;
   constexpr int G = 8 / WV;
   const int q = lane % W, bl = lane / W;
   const word_t* p = line_of<T>(words, P, wid, 0) + WV * q;
   T sum = T(0);
-  for (int b0 = 0; b0 < P; b0 += NB * G) {
-    word_t w[G][WV];
-    const bool ok = poll([&] {
-      bool right = true;
+  if constexpr (STAGED) {
+    if (!take_staged<T, W>(line_of<T>(words, P, wid, 0), LINE * WV, P, leads_group(blockIdx.x), alone, nq, tag, lane, sum))
+      return false;
+  } else {
+    for (int b0 = 0; b0 < P; b0 += NB * G) {
+      word_t w[G][WV];
+      const bool ok = poll([&] {
+        bool right = true;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int b = b0 + NB * g + bl;
-        if (NB * g + b0 < P)
+        for (int g = 0; g < G; ++g) {
+          const int b = b0 + NB * g + bl;
+          if (NB * g + b0 < P)
 #pragma unroll
-          for (int h = 0; h < WV; ++h) w[g][h] = get_word(p + (unsigned)((b < P ? b : P - 1) * LINE * WV + h));
-      }
+            for (int h = 0; h < WV; ++h) w[g][h] = get_word(p + (unsigned)((b < P ? b : P - 1) * LINE * WV + h));
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          if (NB * g + b0 < P)
+#pragma unroll
+            for (int h = 0; h < WV; ++h) right = right && ((unsigned int)w[g][h] == tag || q >= nq);
+        return right;
+      });
+      if (!ok) return false;
 #pragma unroll
       for (int g = 0; g < G; ++g)
-        if (NB * g + b0 < P)
-#pragma unroll
-          for (int h = 0; h < WV; ++h) right = right && ((unsigned int)w[g][h] == tag || q >= nq);
-      return right;
-    });
-    if (!ok) return false;
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-      if (NB * g + b0 < P && NB * g + b0 + bl < P && q < nq) sum += word_value(w[g], T(0));
+        if (NB * g + b0 < P && NB * g + b0 + bl < P && q < nq) sum += word_value(w[g], T(0));
+    }
+    sum = lane_sum<W>(sum);
   }
-  sum = lane_sum<W>(sum);
   // lane q holds the sum of value q; hand each to every lane
   if (lane < nq) all[wid + SMALL_NW * lane] = sum;
 #pragma unroll
@@ -80,34 +163,42 @@ __device__ __forceinline__ bool collect(word_t* words, int P, int wid, int lane,
 }
 
 // one value a block, in a line of its own: the sum over the blocks
-template <typename T>
-__device__ __forceinline__ bool collect_one(const word_t* words, int P, int lane, unsigned int tag, T& out) {
+// (past 64 blocks `leader`: this wave sums its group's for the others).
+template <typename T, bool STAGED>
+__device__ __forceinline__ bool collect_one(word_t* words, int P, int lane, unsigned int tag, T& out,
+                                            bool leader = false, bool alone = false) {
   constexpr int WV = small_words_per_value<T>();
-  constexpr int L = SMALL_MAX_P / WAVE;
-  word_t w[L][WV];
-  const bool ok = poll([&] {
-    bool all = true;
+  if constexpr (STAGED) {
+    T s;
+    if (!take_staged<T, 1>(words, LINE, P, leader, alone, 1, tag, lane, s)) return false;
+    out = read_lane(s, 0);
+  } else {
+    word_t w[WV];
+    const bool ok = poll([&] {
+      bool all = true;
 #pragma unroll
-    for (int l = 0; l < L; ++l) {
-      const int b = lane + WAVE * l;
-      if (WAVE * l < P)
+      for (int h = 0; h < WV; ++h) w[h] = get_word(words + (unsigned)((lane < P ? lane : P - 1) * LINE + h));
 #pragma unroll
-        for (int h = 0; h < WV; ++h) w[l][h] = get_word(words + (unsigned)((b < P ? b : P - 1) * LINE + h));
-    }
-#pragma unroll
-    for (int l = 0; l < L; ++l)
-      if (WAVE * l < P)
-#pragma unroll
-        for (int h = 0; h < WV; ++h) all = all && (unsigned int)w[l][h] == tag;
-    return all;
-  });
-  if (!ok) return false;
-  T s = T(0);
-#pragma unroll
-  for (int l = 0; l < L; ++l)
-    if (lane + WAVE * l < P) s += word_value(w[l], T(0));
-  out = lane_sum<1>(s);
+      for (int h = 0; h < WV; ++h) all = all && (unsigned int)w[h] == tag;
+      return all;
+    });
+    if (!ok) return false;
+    out = lane_sum<1>(lane < P ? T(0) + word_value(w, T(0)) : T(0));
+  }
   return true;
+}
+
+// the same in the single phases
+template <typename T, int SLOTS>
+__device__ __forceinline__ bool collect_alone(word_t* words, int P, int wid, int lane, unsigned int tag, T (&out)[SLOTS],
+                                              T* all, int nq) {
+  return small_staged(P) ? collect<T, SLOTS, true>(words, P, wid, lane, tag, out, all, nq, true)
+                         : collect<T, SLOTS, false>(words, P, wid, lane, tag, out, all, nq);
+}
+template <typename T>
+__device__ __forceinline__ bool collect_one_alone(word_t* words, int P, int lane, unsigned int tag, T& out) {
+  return small_staged(P) ? collect_one<T, true>(words, P, lane, tag, out, false, true)
+                         : collect_one<T, false>(words, P, lane, tag, out);
 }
 
 // A block's rows of V in memory (the single phases): column c, local row i, 0 past n.
@@ -210,8 +301,8 @@ __device__ __forceinline__ T small_updated(const T* part, T w, int rows, int i) 
 // words (tag `tag`) of the unnormalised vector; the products and their order
 // are those of sell_row.  The norm's sum is polled behind the first round's
 // gathers, which are in flight meanwhile.
-template <typename T, typename S, int U>
-__device__ __forceinline__ bool gather_row(const Csr& A, const word_t* x, unsigned int tag, const word_t* norm, int P,
+template <typename T, typename S, int U, bool STAGED>
+__device__ __forceinline__ bool gather_row(const Csr& A, const word_t* x, unsigned int tag, word_t* norm, int P,
                                            int r, int lane, int base, int K, bool& have_inv, T& inv, T& y) {
 #pragma clang fp contract(off)
   constexpr int WV = small_words_per_value<T>();
@@ -245,7 +336,7 @@ __device__ __forceinline__ bool gather_row(const Csr& A, const word_t* x, unsign
     load();
     if (!have_inv) {
       T n2;
-      if (!collect_one(norm, P, lane, tag, n2)) return false;
+      if (!collect_one<T, STAGED>(norm, P, lane, tag, n2)) return false;
       inv = T(1) / sqrt(n2);
       have_inv = true;
     }
@@ -281,8 +372,8 @@ struct Window : WindowMap<win_chunks<T>(), 512, SMALL_MAX_RL> {
 // Loads the window's rows (words with tag `tag`), scaled and rounded to the
 // next basis vector, by the worker waves; the norm is polled behind the first
 // batch of loads.
-template <typename T, typename S>
-__device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n, unsigned int tag, const word_t* norm,
+template <typename T, typename S, bool STAGED>
+__device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n, unsigned int tag, word_t* norm,
                                             int P, int wid, int lane, bool have_inv, T& inv) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int G = 4;
@@ -312,7 +403,7 @@ __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n
     load();
     if (!have_inv) {
       T n2;
-      if (!collect_one(norm, P, lane, tag, n2)) return false;
+      if (!collect_one<T, STAGED>(norm, P, lane, tag, n2)) return false;
       inv = T(1) / sqrt(n2);
       have_inv = true;
     }
@@ -335,11 +426,13 @@ __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n
 // multiply-adds a lane and reads no V (kept in LDS, the sweeps took half of an
 // iteration: 64^2, fp32: 6.8 instead of 4.5 ms a solve).
 //
-// Bound by the latency of the three exchanges, about 1.1 us each at 32 blocks.
-// GMRES(50) to 1e-12, whole solves, against one kernel per operation: 64^2
-// fp32 15.1 -> 4.5 ms, 171^2 fp64 26.1 -> 10.4, 27-point 45^3 with a bf16
-// basis 11.9 -> 5.2, 500^2 68.3 -> 34.2; GMRES(100), 7-point 50^3 30.2 -> 16.5.
-template <typename T, typename S, int SLOTS, int RL>
+// Bound by the latency of the three exchanges, 1.1 us each at 32 blocks, 1.8 us
+// in two stages.  GMRES(50) to 1e-12, whole solves, against one kernel per
+// operation: 64^2 fp32 13.3 -> 3.7 ms, 171^2 fp64 29.3 -> 11.2, 27-point 45^3
+// with a bf16 basis 11.6 -> 4.0, 500^2 68.3 -> 26.0; GMRES(100), 7-point 50^3
+// 30.2 -> 9.6 (the two stages alone, against every block reading every line:
+// 45^3 5.1 -> 4.0, 500^2 33.8 -> 26.0, 50^3 16.4 -> 9.6).
+template <typename T, typename S, int SLOTS, int RL, bool STAGED>
 __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int ROWS = WAVE * RL;
@@ -366,8 +459,8 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     sh.g = (T)a.st.g[0];
   }
   word_t* const h1w = a.words;
-  word_t* const h2w = h1w + (size_t)SMALL_NW * P * LINE * WV;
-  word_t* const nw = h2w + (size_t)SMALL_NW * P * LINE * WV;
+  word_t* const h2w = h1w + (size_t)SMALL_NW * (P + SMALL_GROUPS) * LINE * WV;
+  word_t* const nw = h2w + (size_t)SMALL_NW * (P + SMALL_GROUPS) * LINE * WV;
   if (worker)
     for (int i = wid * WAVE + lane; i < ROWS; i += SMALL_NW * WAVE) {
       s_w[i] = T(0);
@@ -399,7 +492,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     if (nq > 0) {
       publish<T, SLOTS>(words, P, wid, lane, tag, acc, nq);
       __builtin_amdgcn_s_sleep(POLL_WAIT);
-      ok = collect<T, SLOTS>(words, P, wid, lane, tag, h, all, nq);
+      ok = collect<T, SLOTS, STAGED>(words, P, wid, lane, tag, h, all, nq);
     }
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
@@ -427,10 +520,10 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     __builtin_amdgcn_s_sleep(POLL_WAIT);
     if (worker) {
       if (win.chunks > 0)
-        lost = !window_load<T, S>(win, a.x, n, tag - 1, nw, P, wid, lane, j == 0, inv);
+        lost = !window_load<T, S, STAGED>(win, a.x, n, tag - 1, nw, P, wid, lane, j == 0, inv);
     } else if (j > 0) {
       T n2 = T(0);
-      lost = !collect_one(nw, P, lane, tag - 1, n2);
+      lost = !collect_one<T, STAGED>(nw, P, lane, tag - 1, n2, leads_group(blockIdx.x));
       if (lane == 0) sh.nrm2 = n2;
     }
     __syncthreads();
@@ -446,10 +539,10 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
           } else {
             const int base = a.A.sptr[sl];
             const int K = (a.A.sptr[sl + 1] - base) / SELL_C;
-            lost = !gather_row<T, S, 5>(a.A, a.x, tag - 1, nw, P, r, lane, base, K, have_inv, inv, y);
+            lost = !gather_row<T, S, 5, STAGED>(a.A, a.x, tag - 1, nw, P, r, lane, base, K, have_inv, inv, y);
             if (!have_inv && !lost) {  // a slice without entries
               T n2 = T(0);
-              lost = !collect_one(nw, P, lane, tag - 1, n2);
+              lost = !collect_one<T, STAGED>(nw, P, lane, tag - 1, n2);
               inv = T(1) / sqrt(n2);
               have_inv = true;
             }
@@ -509,7 +602,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     if (j + 1 >= a.kmax) {
       if (!worker) {
         T n2 = T(0);
-        lost = !collect_one(nw, P, lane, tag, n2);
+        lost = !collect_one<T, STAGED>(nw, P, lane, tag, n2, leads_group(blockIdx.x));
         if (lane == 0) {
           sh.nrm2 = n2;
           if (lost) sh.lost = 1;
@@ -547,8 +640,8 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
   const bool worker = wid < SMALL_NW;
   const int r0 = blockIdx.x * rows;
   word_t* const h1w = a.words;
-  word_t* const h2w = h1w + (size_t)SMALL_NW * P * LINE * WV;
-  word_t* const nw = h2w + (size_t)SMALL_NW * P * LINE * WV;
+  word_t* const h2w = h1w + (size_t)SMALL_NW * (P + SMALL_GROUPS) * LINE * WV;
+  word_t* const nw = h2w + (size_t)SMALL_NW * (P + SMALL_GROUPS) * LINE * WV;
   const unsigned int tag = a.tag + (unsigned int)j;
   const int nq = worker && wid <= j ? (j - wid) / SMALL_NW + 1 : 0;
   const VGlobal<T, S> V{a.V + r0, a.ldv, n - r0};
@@ -559,12 +652,12 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     const StateHdr* hd = a.st.hdr;
     if (worker) {
       if (nq > 0) {
-        lost = !collect<T, SLOTS>(h1w, P, wid, lane, tag, h, sh.h1[j & 1], nq);
-        lost = !collect<T, SLOTS>(h2w, P, wid, lane, tag, h, sh.h2, nq) || lost;
+        lost = !collect_alone<T, SLOTS>(h1w, P, wid, lane, tag, h, sh.h1[j & 1], nq);
+        lost = !collect_alone<T, SLOTS>(h2w, P, wid, lane, tag, h, sh.h2, nq) || lost;
       }
     } else {
       T n2 = T(0);
-      lost = !collect_one(nw, P, lane, tag, n2);
+      lost = !collect_one_alone(nw, P, lane, tag, n2);
       for (int i = lane; i < j; i += WAVE) {
         sh.cs[i] = (T)a.st.cs[i];
         sh.sn[i] = (T)a.st.sn[i];
@@ -582,7 +675,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     T inv = (T)a.st.hdr->inv_h;
     if (j > 0) {
       T n2 = T(0);
-      lost = !collect_one(nw, P, lane, tag - 1, n2);
+      lost = !collect_one_alone(nw, P, lane, tag - 1, n2);
       inv = T(1) / sqrt(n2);
     }
     const XScaled<T, S> xs{a.wtmp, inv};
@@ -610,7 +703,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     constexpr bool FIRST = PH == SMALL_UPDATE;
     const T* in = FIRST ? a.w1 : a.w2;
     T* out = FIRST ? a.w2 : a.wtmp;
-    if (nq > 0) lost = !collect<T, SLOTS>(FIRST ? h1w : h2w, P, wid, lane, tag, h, sh.h2, nq);
+    if (nq > 0) lost = !collect_alone<T, SLOTS>(FIRST ? h1w : h2w, P, wid, lane, tag, h, sh.h2, nq);
     if (worker) small_partial<T, SLOTS>(part, V, h, rows, j, wid, lane);
     __syncthreads();
     T nrm = T(0);
@@ -659,56 +752,59 @@ SmallKernel<T, S> phase_of(SmallPhase ph) {
 }
 
 // Rows per lane of the instances: SLOTS x RL values of T take at most 128 of
-// the 256 registers a lane has.
-template <typename T, typename S, int SLOTS, int RL>
-SmallKernel<T, S> cycle_of(int rl) {
-  if constexpr (SLOTS * RL * (int)sizeof(T) > 128 * 4) {
+// a lane's registers.
+constexpr int RLS[] = {2, 3, 4, 6, 8, 12, SMALL_MAX_RL};
+template <typename T, typename S, int SLOTS, int I>
+SmallKernel<T, S> cycle_of(int rl, bool staged) {
+  if constexpr (I == sizeof(RLS) / sizeof(int)) {
+    return nullptr;
+  } else if constexpr (SLOTS * RLS[I] * (int)sizeof(T) > 128 * 4) {
     return nullptr;
   } else {
-    if (rl == RL) return k_small_cycle<T, S, SLOTS, RL>;
-    constexpr int NEXT = RL == 1 ? 2 : RL == 2 ? 3 : RL == 3 ? 4 : RL == 4 ? 6 : RL == 6 ? 8 : RL == 8 ? 12 : 16;
-    if constexpr (RL == 16) return nullptr;
-    else return cycle_of<T, S, SLOTS, NEXT>(rl);
+    if (rl != RLS[I]) return cycle_of<T, S, SLOTS, I + 1>(rl, staged);
+    if constexpr (RLS[I] >= SMALL_STAGED_RL)
+      if (staged) return k_small_cycle<T, S, SLOTS, RLS[I], true>;
+    if constexpr (RLS[I] <= SMALL_STAGED_RL)
+      if (!staged) return k_small_cycle<T, S, SLOTS, RLS[I], false>;
+    return nullptr;
   }
 }
-
-constexpr int RLS[] = {1, 2, 3, 4, 6, 8, 12, SMALL_MAX_RL};
 
 int slots_of(int m) { return m <= 4 * SMALL_NW ? 4 : m <= 8 * SMALL_NW ? 8 : 16; }
 
 }  // namespace
 
 template <typename T, typename S>
-SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows) {
+SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows, int blocks) {
   const int sl = slots_of(m);
   if (ph == SMALL_CYCLE)
-    return sl == 4   ? cycle_of<T, S, 4, 1>(rows / WAVE)
-           : sl == 8 ? cycle_of<T, S, 8, 1>(rows / WAVE)
-                     : cycle_of<T, S, 16, 1>(rows / WAVE);
+    return sl == 4   ? cycle_of<T, S, 4, 0>(rows / WAVE, small_staged(blocks))
+           : sl == 8 ? cycle_of<T, S, 8, 0>(rows / WAVE, small_staged(blocks))
+                     : cycle_of<T, S, 16, 0>(rows / WAVE, small_staged(blocks));
   return sl == 4 ? phase_of<T, S, 4>(ph) : sl == 8 ? phase_of<T, S, 8>(ph) : phase_of<T, S, 16>(ph);
 }
-template SmallKernel<float, float> small_kernel<float, float>(SmallPhase, int, int);
-template SmallKernel<float, bf16_t> small_kernel<float, bf16_t>(SmallPhase, int, int);
-template SmallKernel<double, double> small_kernel<double, double>(SmallPhase, int, int);
+template SmallKernel<float, float> small_kernel<float, float>(SmallPhase, int, int, int);
+template SmallKernel<float, bf16_t> small_kernel<float, bf16_t>(SmallPhase, int, int, int);
+template SmallKernel<double, double> small_kernel<double, double>(SmallPhase, int, int, int);
 
-// An exchange's time grows with the lines a wave reads: 1.1 us at 16 blocks,
-// 1.6 us at 64, 2.4 us at 128, 5 us at 256 (one 128-byte line per block in
-// fp32, two in fp64); more rows per block cost registers and time in between.
-// So: at least 128 rows (4096 rows, fp32: 32 blocks 4.5 ms a solve, 16 blocks
-// 4.6, 8 blocks 5.5), and as many as bring the blocks' lines to 128 (29241
-// rows, fp64: 153 blocks 13.5 ms, 115 11.7, 77 10.5, 58 10.4; 91125 rows,
-// bf16 basis: 238 blocks 5.8 ms, 178 5.6, 119 5.2, 89 6.0), or as many as the
-// registers hold.
+// An exchange of every block with every other grows with the lines a wave
+// reads (1.1 us at 16 blocks, 1.6 at 64, 2.4 at 128, 5 at 256); in two stages
+// it takes 1.8 us for all 256.  More rows per block cost registers and time in
+// between.  So: at least 128 rows and at most 64 blocks as long as that takes
+// no more than 256 rows a block (4096 rows, fp32: 64 blocks 4.8 ms a solve, 32
+// 4.7, 16 4.9; 10000: 53 blocks 5.5, 40 5.4, 20 6.0), past that 256 rows or as
+// many more as up to 256 blocks ask for (40000: 157 blocks 10.1, 105 10.1, 53
+// 10.6; 160000: 209 blocks 18.2, 157 22.6; fp64 29241: 153 blocks 10.3, 115
+// 10.2, 58 10.6; 62500: 245 blocks 17.4, 163 17.0, 123 18.4).
 int small_rows(int64_t n, int m, int sT, int cus) {
   if (m > SMALL_MAX_M) return 0;
   const int64_t blocks = std::min(SMALL_MAX_P, cus);
-  int rows = 0;
   for (int rl : RLS) {
     if (slots_of(m) * rl * sT > 128 * 4) break;
-    rows = WAVE * rl;
-    if (rl >= 2 && n * (sT / 4) <= 128 * (int64_t)rows) break;
+    const int64_t rows = WAVE * rl, most = rl < SMALL_STAGED_RL ? std::min<int64_t>(blocks, WAVE) : blocks;
+    if (n <= rows * most) return rl > SMALL_STAGED_RL && n <= rows * WAVE ? 0 : (int)rows;  // 0: fewer compute units
   }
-  return n <= rows * blocks ? rows : 0;
+  return 0;
 }
 
 size_t small_cycle_lds(int rows, int sT) {
@@ -722,7 +818,7 @@ size_t small_phase_lds(int rows, int sT) { return (size_t)rows * (SMALL_NW + 1) 
 
 size_t small_words(int blocks, int sT) {
   const size_t WV = sT / 4;
-  return (2 * SMALL_NW * WV + 1) * (size_t)blocks * LINE;
+  return (2 * SMALL_NW * WV + 1) * (size_t)(blocks + SMALL_GROUPS) * LINE;
 }
 
 void small_clear(unsigned long long* words, size_t count, hipStream_t s) {

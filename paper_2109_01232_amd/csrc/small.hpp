@@ -29,6 +29,7 @@ constexpr int SMALL_MAX_M = 16 * SMALL_NW;           // restart lengths of this 
 constexpr int SMALL_MAX_RL = 16;                     // rows per lane (64 RL rows per block)
 constexpr size_t SMALL_LDS = 160 << 10;              // of a compute unit
 constexpr int SMALL_MAX_P = 256;                     // blocks
+constexpr int SMALL_GROUPS = 16;                     // of up to 16 blocks: an exchange's second stage
 constexpr size_t SMALL_WORDS_AT = (size_t)MAX_BLOCKS * 8;  // the words follow the partials of the cycle's set-up
 
 enum SmallPhase { SMALL_SPMV = 0, SMALL_GIVENS, SMALL_UPDATE, SMALL_NORM, SMALL_CYCLE };
@@ -42,7 +43,7 @@ struct SmallArgs {
   S* V;
   long ldv;
   State st;
-  unsigned long long* words;  // partial sums: h1, h2 (a line per wave and block), norm (a line per block)
+  unsigned long long* words;  // partial sums: h1, h2 (a line per wave and block, then per group), norm (a line per block, group)
   unsigned long long* x;      // the unnormalised vector as words (the cycle kernel's gathers)
   unsigned int tag;           // of the cycle, > 1; iteration j uses tag + j, the gathers of j = 0 tag - 1
   unsigned int vals_lds;  // dynamic LDS of the cycle kernel: the block's rows of A, if they fit
@@ -63,7 +64,7 @@ size_t small_phase_lds(int rows, int sT);
 template <typename T, typename S>
 using SmallKernel = void (*)(SmallArgs<T, S>);
 template <typename T, typename S>
-SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows);
+SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows, int blocks);
 
 // words of the partial sums
 size_t small_words(int blocks, int sT);

@@ -120,6 +120,16 @@ def test_wide_rows_and_rows_gathered_one_by_one(inner, basis):
     assert dc["status"] == dp["status"] and torch.equal(xc, xp) and np.array_equal(hc, hp)
 
 
+@pytest.mark.parametrize("inner,basis", KINDS)
+@pytest.mark.parametrize("n", [64 * 256, 64 * 256 + 1, 72 * 256, 73 * 256 - 1, 128 * 256, 128 * 256 + 1, 200 * 256 + 3, 65537])
+def test_exchange_in_one_and_two_stages(n, inner, basis):
+    """64 blocks (every block reads every line), 65 and more (groups of up to
+    16 blocks of a die first: one of nine blocks, full ones, a second per die
+    of one block and of several)."""
+    say("small stages", n, inner, basis)
+    both(banded(n, (-600, -1, 0, 1, 600), n), 40, inner, basis, 43, oracle=False)
+
+
 def test_threads_and_streams():
     """Four threads, each with its own stream and workspace, solve different
     systems at the same time: the bits of solving alone."""
