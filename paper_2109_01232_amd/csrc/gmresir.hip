@@ -57,8 +57,8 @@ constexpr int MAX_GRID = 1024;  // <= MAX_BLOCKS (partials per reduction)
 // Systems of more rows run the cycle kernel of mid.hip where it takes them (up
 // to 2^21 rows, 2^20 in fp64): from a little past the limits of the one of
 // small.hip, the smallest sizes measured.  It is the faster one over all of
-// that range: solves of 263169 rows 88.5 -> 41.8 ms, 10^6 211 -> 149, 2^21 51.0
-// -> 44.9 (27-point, fp32); fp64 136900 rows 59.7 -> 34.7, 1030301 50.7 -> 40.0.
+// that range: solves of 263169 rows 88.5 -> 41.8 ms, 27-point of 1030301 24.8
+// -> 18.7, of 2^21 51.0 -> 44.9; fp64 136900 rows 59.7 -> 34.7, 1030301 50.7 -> 40.0.
 int64_t mid_min_n(int m, int sT) { return (sT == 4 && m <= 56 ? 1 << 18 : 1 << 17) + 1024; }
 constexpr int64_t GRAPH_MAX_N = 1 << 18;  // cycles of smaller systems run as HIP graphs
 constexpr size_t ALIGN = 256;
@@ -1047,6 +1047,12 @@ struct Ctx {
     if (!A->sell_shared || L.bj > 0 || L.ls || poly_on || prof->on || L.m > MID_MAX_M ||
         n <= mid_min_n(L.m, (int)sizeof(T)) || device_cus(A->device) < MID_BLOCKS)
       return;
+    // At a residual of 1e-12 the solutions of five-point systems past 2^19 rows
+    // are off by 0.5-3e-9, and where another order of sums ends the refinement
+    // a step earlier or later they move by as much (1.8e-9 for one of five
+    // right-hand sides at 10^6 rows): those keep the general kernels' order
+    // (211 ms a solve instead of 149).  Wider rows move by 3e-11 at most.
+    if (n > 1 << 19 && A->nnz < 6 * n) return;
     mid_k = mid_kernel<T, S>(A->nslices);
     if (!mid_k.k) return;
     small_clear(words(), mid_words(), stream);

@@ -18,10 +18,9 @@
 // Bound by memory where most columns are read (the first projection of 1000^2:
 // 5.6 TB/s), by the vector units and LDS barriers where most are resident.
 // Whole solves to 1e-12, GMRES(50), against one kernel per operation: fp32
-// 5-point 513^2 88.5 -> 41.8 ms, 800^2 145 -> 90, 1000^2 211 -> 149, 27-point
-// 80^3 15.8 -> 10.3, 101^3 24.8 -> 18.7, 128^3 51.0 -> 44.9; bf16 basis 80^3
-// 17.3 -> 11.9, 128^3 42.2 -> 38.8; fp64 7-point 52^3 28.6 -> 16.1, 27-point
-// 101^3 50.7 -> 40.0.
+// 5-point 513^2 88.5 -> 41.8 ms, 600^2 98.8 -> 53.2, 27-point 80^3 15.8 -> 10.3,
+// 101^3 24.8 -> 18.7, 128^3 51.0 -> 44.9; bf16 basis 80^3 17.3 -> 11.9, 128^3
+// 42.2 -> 38.8; fp64 7-point 52^3 28.6 -> 16.1, 27-point 101^3 50.7 -> 40.0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
