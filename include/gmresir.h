@@ -108,7 +108,8 @@ typedef struct {
                           iteration (delayed reorthogonalisation, Bielich et al., Parallel Computing
                           2022): one reduction and two sweeps of the basis per iteration, results
                           equal to CGS2's in exact arithmetic.  1 needs basis_prec = inner_prec
-                          (no BF16) and restart <= 128. */
+                          (no BF16) and restart <= 128.  Where a cycle is one kernel (see
+                          gmresir_solve) it makes the two passes of 0, which are faster there. */
 } gmresir_params;
 
 typedef struct {
@@ -188,12 +189,12 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    refinement.  b = 0 gives x = 0 and GMRESIR_OK.
    How a cycle is launched (profile = 0) depends on the system's size.  Where
    the basis fits the registers of the GPU's compute units (layout 3, no
-   preconditioner, ortho 0, restart <= 112; up to 262144 rows in fp32 and
+   preconditioner, restart <= 112; up to 262144 rows in fp32 and
    131072 in fp64 at restart 50) it is one cooperative kernel, whose blocks
    wait for each other inside it; HIP errors when one of them does not answer
    for a minute.  So it is, with only the first columns of the basis in
    registers, for larger systems of such matrices up to 2^21 rows (2^20 in
-   fp64) at restart <= 64, if the rows of x that a 256th of the rows reach fit
+   fp64, 2^19 at fewer than 6 nonzeros a row) at restart <= 64, if the rows of x that a 256th of the rows reach fit
    a compute unit's LDS.  Other systems of n <= 2^18 record the kernels of a
    cycle once as a HIP graph, replayed for every later cycle of the same
    length.  With profile = 1 and in gmresir_solve_noalloc every kernel is

@@ -1044,7 +1044,7 @@ struct Ctx {
   MidKernel<T, S> mid_k{};
 
   void mid_init() {
-    if (!A->sell_shared || L.bj > 0 || L.ls || poly_on || prof->on || L.m > MID_MAX_M ||
+    if (!A->sell_shared || L.bj > 0 || poly_on || prof->on || L.m > MID_MAX_M ||
         n <= mid_min_n(L.m, (int)sizeof(T)) || device_cus(A->device) < MID_BLOCKS)
       return;
     // At a residual of 1e-12 the solutions of five-point systems past 2^19 rows
@@ -1053,6 +1053,9 @@ struct Ctx {
     // right-hand sides at 10^6 rows): those keep the general kernels' order
     // (211 ms a solve instead of 149).  Wider rows move by 3e-11 at most.
     if (n > 1 << 19 && A->nnz < 6 * n) return;
+    // ortho 1 reads the basis twice an iteration: faster than three times in
+    // part past 2^20 rows (1157625: 23.1, 24.2 ms; 512000: 13.1, 10.2)
+    if (L.ls && n > 1 << 20) return;
     mid_k = mid_kernel<T, S>(A->nslices);
     if (!mid_k.k) return;
     small_clear(words(), mid_words(), stream);
@@ -1079,10 +1082,14 @@ struct Ctx {
     return true;
   }
 
-  // called once the solve's options are known, before its first cycle
+  // called once the solve's options are known, before its first cycle.  A
+  // cycle in one kernel makes two-pass CGS2 with ortho 1 too: what the delayed
+  // second pass saves, a reduction's launches, costs nothing there, and its
+  // basis is no less orthogonal (1600 rows 7.8 -> 2.5 ms a solve, 64000 at
+  // restart 100 17.9 -> 6.1, 250000 52.6 -> 26.1).
   void small_init(bool coop, bool mid) {
     if (mid) mid_init();
-    if (mid_k.k || !A->sell_shared || L.bj > 0 || L.ls || poly_on) return;
+    if (mid_k.k || !A->sell_shared || L.bj > 0 || poly_on) return;
     small_R = small_rows(n, L.m, (int)sizeof(T), device_cus(A->device));
     if (small_R == 0) return;
     small_P = (n + small_R - 1) / small_R;
