@@ -188,18 +188,20 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    to the right-hand side of its cycle.  The stream is synchronised once per
    refinement.  b = 0 gives x = 0 and GMRESIR_OK.
    How a cycle is launched (profile = 0) depends on the system's size.  Where
-   the basis fits the registers of the GPU's compute units (layout 3, no
-   preconditioner, restart <= 112; up to 262144 rows in fp32 and
-   131072 in fp64 at restart 50) it is one cooperative kernel, whose blocks
-   wait for each other inside it; HIP errors when one of them does not answer
-   for a minute.  So it is, with only the first columns of the basis in
-   registers, for larger systems of such matrices up to 2^21 rows (2^20 in
-   fp64, 2^19 at fewer than 6 nonzeros a row) at restart <= 64, if the rows of x that a 256th of the rows reach fit
-   a compute unit's LDS.  Other systems of n <= 2^18 record the kernels of a
-   cycle once as a HIP graph, replayed for every later cycle of the same
-   length.  With profile = 1 and in gmresir_solve_noalloc every kernel is
-   launched directly; the bits are the same, but for the larger systems: their
-   cycle kernel sums in another order. */
+   the basis fits the registers of the GPU's compute units (layout 3, restart
+   <= 112; up to 262144 rows in fp32 and 131072 in fp64 at restart 50) it is one
+   cooperative kernel, whose blocks wait for each other inside it; HIP errors
+   when one of them does not answer for a minute.  With a preconditioner that
+   asks for a block size dividing 64 or poly_prec 0, and for rows that exchange
+   values to lie at most 31 of the kernel's blocks apart.  So it is, with only
+   the first columns of the basis in registers, for larger systems without a
+   preconditioner up to 2^21 rows (2^20 in fp64 or with ortho 1, 2^19 at fewer
+   than 6 nonzeros a row) at restart <= 64, if the rows of x that a 256th of the
+   rows reach fit a compute unit's LDS.  Other systems of n <= 2^18 record the
+   kernels of a cycle once as a HIP graph, replayed for every later cycle of the
+   same length.  With profile = 1 and in gmresir_solve_noalloc every kernel is
+   launched directly; the bits are the same, but for the larger systems and with
+   a preconditioner: there the cycle kernel sums in another order. */
 int gmresir_solve(const gmresir_matrix* A, const double* b, double* x, const gmresir_params* p,
                   const double* poly_roots_host, void* ws, size_t ws_bytes, gmresir_result* res_host,
                   double* hist_host, int64_t hist_cap, void* stream);

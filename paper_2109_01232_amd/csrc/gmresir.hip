@@ -1082,6 +1082,9 @@ struct Ctx {
     return true;
   }
 
+  bool small_pre = false;  // with a preconditioner in the cycle kernel
+  int small_far = 0;       // distance of blocks that exchange rows
+
   // called once the solve's options are known, before its first cycle.  A
   // cycle in one kernel makes two-pass CGS2 with ortho 1 too: what the delayed
   // second pass saves, a reduction's launches, costs nothing there, and its
@@ -1089,11 +1092,33 @@ struct Ctx {
   // restart 100 17.9 -> 6.1, 250000 52.6 -> 26.1).
   void small_init(bool coop, bool mid) {
     if (mid) mid_init();
-    if (mid_k.k || !A->sell_shared || L.bj > 0 || poly_on) return;
+    // a preconditioner runs inside the cycle where its blocks lie in the slices
+    // and the LDS has room for the polynomial's vectors; every size that
+    // qualifies is faster (900 rows 4.0 -> 1.0 ms a solve, 216000 18.7 -> 16.4)
+    const bool pre = L.bj > 0 || poly_on;
+    if (mid_k.k || !A->sell_shared) return;
     small_R = small_rows(n, L.m, (int)sizeof(T), device_cus(A->device));
     if (small_R == 0) return;
     small_P = (n + small_R - 1) / small_R;
     small_coop = coop && !prof->on;
+    if (pre) {
+      const size_t rows = (size_t)SMALL_PRE_ROWS * small_R * sizeof(T);
+      if (!small_coop || poly32 || (L.bj > 0 && WAVE % L.bj != 0) ||
+          rows > small_cycle_lds(small_R, (int)sizeof(T)) ||
+          small_words(small_P, (int)sizeof(T)) * 8 > SMALL_PROG_AT - SMALL_WORDS_AT) {
+        small_R = 0;
+        return;
+      }
+      small_pre = true;
+      small_near(Ain, (int)sizeof(T), small_R, small_P, &st.hdr->wide, stream);  // read with the first residual
+      if (poly_on) {
+        std::vector<SmallStep> steps;
+        for (const PStep& p : prog)
+          steps.push_back({{p.ay, p.aw, p.ax, p.at, p.bw, p.bx, p.bt}, p.w, p.d, p.has_y, p.y_read});
+        (void)hipMemcpyAsync((char*)part + SMALL_PROG_AT, steps.data(), steps.size() * sizeof(SmallStep),
+                             hipMemcpyHostToDevice, stream);
+      }
+    }
     small_clear(words(), small_words(small_P, (int)sizeof(T)), stream);
     // the vector as words lies in w1 and w2 (adjacent; used by the phases only)
     if (small_coop) small_clear((unsigned long long*)w1, (size_t)L.ldv * sizeof(T) * 2 / 8, stream);
@@ -1116,6 +1141,16 @@ struct Ctx {
     a.blocks = small_P;
     a.j = j;
     a.kmax = kmax;
+    if (small_pre) {
+      a.bj = L.bj;
+      a.steps = poly_on ? (int)prog.size() : 0;
+      a.near = small_far;
+      a.minv = minv;
+      a.prog = (const SmallStep*)((char*)part + SMALL_PROG_AT);
+      a.z = (unsigned long long*)z;  // z, py and p0, p1: pairs of adjacent vectors
+      a.z1 = (unsigned long long*)p0;
+      a.vals_lds -= (unsigned)(SMALL_PRE_ROWS * small_R * sizeof(T));
+    }
     return a;
   }
 
@@ -1144,12 +1179,28 @@ struct Ctx {
     if (small_coop) {
       SmallArgs<T, S> a = small_args(0, kmax);
       void* args[] = {&a};
-      launched = hipLaunchCooperativeKernel((const void*)small_kernel<T, S>(SMALL_CYCLE, L.m, small_R, small_P), dim3(small_P),
-                                            dim3(SMALL_NT), args, a.vals_lds, stream) == hipSuccess;
+      const SmallPhase ph = small_pre ? SMALL_CYCLE_PRE : SMALL_CYCLE;
+      if (small_pre) {  // what the last cycle's end left there must not look like words
+        small_clear(a.z, (size_t)L.ldv * sizeof(T) * 2 / 8, stream);
+        if (poly_on) small_clear(a.z1, (size_t)L.ldv * sizeof(T) * 2 / 8, stream);
+      }
+      launched = hipLaunchCooperativeKernel((const void*)small_kernel<T, S>(ph, L.m, small_R, small_P), dim3(small_P),
+                                            dim3(SMALL_NT), args, (unsigned)small_cycle_lds(small_R, (int)sizeof(T)),
+                                            stream) == hipSuccess;
       if (!launched) {
         (void)hipGetLastError();
         small_coop = false;
       }
+    }
+    if (small_pre && !launched) {
+      small_R = 0;
+      cycle(kmax);
+      return;
+    }
+    for (int j = 0; small_pre && j < kmax; ++j) {
+      if (L.bj > 0) prof->pend.push_back({GMRESIR_CAT_POLY, sT() * n * (L.bj + 2) + sS() * n, j, true, nullptr, nullptr});
+      for (size_t k = 0; poly_on && k < prog.size(); ++k)
+        prof->pend.push_back({GMRESIR_CAT_POLY, spmv_bytes() + sT() * n * 3, j, true, nullptr, nullptr});
     }
     for (int j = 0; j < kmax; ++j)
       for (SmallPhase ph : {SMALL_SPMV, SMALL_UPDATE, SMALL_NORM, SMALL_GIVENS}) small_phase(ph, j, kmax, !launched);
@@ -1312,6 +1363,10 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
   StateHdr H;
   if (int e = c.read_hdr(&H)) return e;
   if (H.wide) c.mid_k.k = nullptr;
+  if (c.small_pre) {
+    c.small_far = H.wide;
+    if (H.wide > SMALL_MAX_NEAR) c.small_R = 0;
+  }
   const double beta = H.beta;
   double gamma = H.gamma;
   int status = GMRESIR_OK;

@@ -1461,13 +1461,6 @@ __global__ void k_fill64(int n, double* __restrict__ x, double v) {
 // polynomial preconditioner: one SpMV step of the product form of p(A)
 // ---------------------------------------------------------------------------
 
-template <typename T>
-struct PolyCoef {
-  T ay, aw, ax, at;  // y = ay*y + aw*W + ax*X + at*(A X)
-  T bw, bx, bt;      // d = bw*W + bx*X + bt*(A X)
-  int has_y, y_read, has_d, has_w;
-};
-
 template <typename T, typename S, bool SCALED>
 struct PolyEpi {
   const T* src;
@@ -1492,11 +1485,9 @@ struct PolyEpi {
     T wr = T(0);
     if (cf.has_w) wr = w_scaled ? Basis<S, T>::round(W[r] * inv) : W[r];
     if (cf.has_y) {
-      T yv = cf.aw * wr + cf.ax * xr + cf.at * t;
-      if (cf.y_read) yv += cf.ay * Y[r];
-      Y[r] = yv;
+      Y[r] = poly_y(cf, wr, xr, t, cf.y_read ? Y[r] : T(0));
     }
-    if (cf.has_d) D[r] = cf.bw * wr + cf.bx * xr + cf.bt * t;
+    if (cf.has_d) D[r] = poly_d(cf, wr, xr, t);
   }
 };
 

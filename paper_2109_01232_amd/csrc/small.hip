@@ -372,7 +372,8 @@ struct Window : WindowMap<win_chunks<T>(), 512, SMALL_MAX_RL> {
 // Loads the window's rows (words with tag `tag`), scaled and rounded to the
 // next basis vector, by the worker waves; the norm is polled behind the first
 // batch of loads.
-template <typename T, typename S, bool STAGED>
+// PLAIN: the words' values as they are.
+template <typename T, typename S, bool STAGED, bool PLAIN = false>
 __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n, unsigned int tag, word_t* norm,
                                             int P, int wid, int lane, bool have_inv, T& inv) {
   constexpr int WV = small_words_per_value<T>();
@@ -401,7 +402,7 @@ __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n
       return off == 0;
     };
     load();
-    if (!have_inv) {
+    if (!PLAIN && !have_inv) {
       T n2;
       if (!collect_one<T, STAGED>(norm, P, lane, tag, n2)) return false;
       inv = T(1) / sqrt(n2);
@@ -415,7 +416,8 @@ __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const int c = c0 + SMALL_NW * g;
-      if (c < W.chunks) W.x[c * SELL_C + lane] = row[g] < 0 ? T(0) : Basis<S, T>::round(word_value(w[g], T(0)) * inv);
+      const T v = word_value(w[g], T(0));
+      if (c < W.chunks) W.x[c * SELL_C + lane] = row[g] < 0 ? T(0) : PLAIN ? v : Basis<S, T>::round(v * inv);
     }
   }
   return true;
@@ -432,7 +434,17 @@ __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n
 // with a bf16 basis 11.6 -> 4.0, 500^2 68.3 -> 26.0; GMRES(100), 7-point 50^3
 // 30.2 -> 9.6 (the two stages alone, against every block reading every line:
 // 45^3 5.1 -> 4.0, 500^2 33.8 -> 26.0, 50^3 16.4 -> 9.6).
-template <typename T, typename S, int SLOTS, int RL, bool STAGED>
+//
+// PRE: z = M v_j first, exchanged block to block as the vector is.  Block
+// Jacobi: one exchange more.  Polynomial: one per SpMV; the vectors alternate
+// between two places, and no block writes a place again before every block
+// within `near` of it (which holds all that read from it) has published the
+// vector after, and so read this one.  2 us an exchange and SpMV, against
+// 5-6 us a launch: 10000 rows, fp32, degree 10 6.6 -> 2.1 ms a solve, block
+// Jacobi 12.9 -> 4.3; 27000 rows, fp64, degree 5 6.4 -> 2.5, block Jacobi 11.2
+// -> 4.6; 125000 27-point rows, degree 20 13.2 -> 4.0, block Jacobi 11.1 -> 5.5;
+// 216000 7-point rows, degree 10 12.4 -> 8.5, block Jacobi 18.7 -> 16.4.
+template <typename T, typename S, int SLOTS, int RL, bool STAGED, bool PRE>
 __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int ROWS = WAVE * RL;
@@ -441,6 +453,8 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
   __shared__ T s_w[ROWS];               // the working vector's rows
   __shared__ T s_part[SMALL_NW][ROWS];  // the waves' parts of V h
   T* s_vals = dyn_lds<T>();             // the rows' values of A, if they fit
+  T* const s_pre = s_vals;              // PRE: rows of v_j, the program's vectors and y
+  if constexpr (PRE) s_vals += SMALL_PRE_ROWS * ROWS;
   const int P = a.blocks, n = a.A.n;
   const int lane = threadIdx.x & (WAVE - 1);
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -510,6 +524,19 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     for (int i = threadIdx.x; i < win.pair[RL] * SELL_C; i += SMALL_NT) s_vals[i] = vals[i];
   const int own = win.chunks > 0 ? win.own * SELL_C : 0;  // the block's rows in win.x
   __syncthreads();
+  // the vector with `tag` at x into the window; every other wave's done too
+  auto exchange_window = [&](word_t* x, unsigned int tag, int near) {
+    bool ok = true;
+    if (worker) {
+      ok = window_load<T, S, STAGED, true>(win, x, n, tag, nullptr, P, wid, lane, true, inv);
+    } else if (near > 0) {
+      const int b = (int)blockIdx.x - near + lane;
+      const bool there = lane <= 2 * near && b >= 0 && b < P;
+      ok = poll([&] { return !there || (unsigned int)get_word(x + (size_t)(there ? b : 0) * ROWS * WV) == tag; });
+    }
+    __syncthreads();
+    return ok;
+  };
   int j = 0;
   for (;; ++j) {
     const unsigned int tag = a.tag + (unsigned int)j;
@@ -527,13 +554,73 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
       if (lane == 0) sh.nrm2 = n2;
     }
     __syncthreads();
+    if constexpr (PRE) {
+      if (worker) {
+        if (wid == j % SMALL_NW) {
+#pragma unroll
+          for (int q = 0; q < SLOTS; ++q)
+            if (q == j / SMALL_NW)
+#pragma unroll
+              for (int i = 0; i < RL; ++i) V[q][i] = r0 / SELL_C + i < a.A.nslices ? win.x[own + lane + WAVE * i] : T(0);
+        }
+        for (int s = wid; s < RL; s += SMALL_NW) {
+          const int i = s * SELL_C + lane, r = r0 + i;
+          const T v = r < n ? win.x[own + i] : T(0);
+          if (r < n) Basis<S, T>::store(a.V + (size_t)j * a.ldv + r, v);
+          if (a.bj > 0) {
+            // as k_bj_apply: the slice is a wave group of 64 / bj blocks
+            const int g = lane / a.bj, m = min(a.bj, n - (r0 + s * SELL_C + g * a.bj));
+            const T* Mg = a.minv + (size_t)(r0 / SELL_C + s) * a.bj * WAVE + lane;
+            const T* xs = &win.x[own + s * SELL_C + g * a.bj];
+            T acc = T(0);
+            if (r < n) {
+              for (int c = 0; c < m; ++c) acc += Mg[(size_t)c * WAVE] * xs[c];
+              put_value(a.z + (size_t)r * WV, acc, tag);
+            }
+          } else {
+            s_pre[i] = v;
+          }
+        }
+      }
+      if (a.bj > 0) {
+        __syncthreads();
+        lost = !exchange_window(a.z, tag, 0) || lost;
+      }
+      for (int k = 0; k < a.steps; ++k) {
+        const SmallStep& ps = a.prog[k];
+        word_t* const to = k & 1 ? a.z1 : a.z;
+        const unsigned int ptag = tag * 256u + (unsigned int)k;
+        const PolyCoef<T> cf = poly_coef<T>(ps.c, ps.has_y, ps.y_read, ps.d, ps.w);
+        T* const Y = s_pre + 4 * ROWS;
+        if (worker)
+          for (int s = wid; s < RL; s += SMALL_NW) {
+            const int i = s * SELL_C + lane, r = r0 + i;
+            if (r0 / SELL_C + s >= a.A.nslices) break;
+            const T t = in_lds ? window_row(win, win.x, s_vals + win.pair[s] * SELL_C, s, lane)
+                               : window_row(win, win.x, vals + win.pair[s] * SELL_C, s, lane);
+            const T xr = win.x[own + i], wr = cf.has_w ? s_pre[ps.w * ROWS + i] : T(0);
+            T out = T(0);
+            if (cf.has_y) {
+              out = poly_y(cf, wr, xr, t, cf.y_read ? Y[i] : T(0));
+              Y[i] = out;
+            }
+            if (cf.has_d) {
+              out = poly_d(cf, wr, xr, t);
+              s_pre[ps.d * ROWS + i] = out;
+            }
+            if (r < n) put_value(to + (size_t)r * WV, out, ptag);
+          }
+        __syncthreads();
+        lost = !exchange_window(to, ptag, a.near) || lost;
+      }
+    }
     if (worker) {
       bool have_inv = j == 0;
       for (int s = wid; s < RL; s += SMALL_NW) {
         const int i = s * SELL_C + lane, r = r0 + i, sl = r0 / SELL_C + s;
         T y = T(0);
         if (sl < a.A.nslices && !lost) {
-          if (win.chunks > 0) {
+          if (PRE || win.chunks > 0) {
             y = in_lds ? window_row(win, win.x, s_vals + win.pair[s] * SELL_C, s, lane)
                        : window_row(win, win.x, vals + win.pair[s] * SELL_C, s, lane);
           } else {
@@ -548,15 +635,15 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
             }
             win.x[i] = r < n ? Basis<S, T>::round(s_w[i] * inv) : T(0);
           }
-          if (r < n) Basis<S, T>::store(a.V + (size_t)j * a.ldv + r, win.x[own + i]);
-          else y = T(0);
+          if (r >= n) y = T(0);
+          else if (!PRE) Basis<S, T>::store(a.V + (size_t)j * a.ldv + r, win.x[own + i]);
         }
         s_w[i] = y;
       }
     }
     __syncthreads();
     if (worker) {
-      if (wid == j % SMALL_NW) {
+      if (!PRE && wid == j % SMALL_NW) {
 #pragma unroll
         for (int q = 0; q < SLOTS; ++q)
           if (q == j / SMALL_NW)
@@ -754,18 +841,18 @@ SmallKernel<T, S> phase_of(SmallPhase ph) {
 // Rows per lane of the instances: SLOTS x RL values of T take at most 128 of
 // a lane's registers.
 constexpr int RLS[] = {2, 3, 4, 6, 8, 12, SMALL_MAX_RL};
-template <typename T, typename S, int SLOTS, int I>
+template <typename T, typename S, int SLOTS, int I, bool PRE>
 SmallKernel<T, S> cycle_of(int rl, bool staged) {
   if constexpr (I == sizeof(RLS) / sizeof(int)) {
     return nullptr;
   } else if constexpr (SLOTS * RLS[I] * (int)sizeof(T) > 128 * 4) {
     return nullptr;
   } else {
-    if (rl != RLS[I]) return cycle_of<T, S, SLOTS, I + 1>(rl, staged);
+    if (rl != RLS[I]) return cycle_of<T, S, SLOTS, I + 1, PRE>(rl, staged);
     if constexpr (RLS[I] >= SMALL_STAGED_RL)
-      if (staged) return k_small_cycle<T, S, SLOTS, RLS[I], true>;
+      if (staged) return k_small_cycle<T, S, SLOTS, RLS[I], true, PRE>;
     if constexpr (RLS[I] <= SMALL_STAGED_RL)
-      if (!staged) return k_small_cycle<T, S, SLOTS, RLS[I], false>;
+      if (!staged) return k_small_cycle<T, S, SLOTS, RLS[I], false, PRE>;
     return nullptr;
   }
 }
@@ -774,13 +861,38 @@ int slots_of(int m) { return m <= 4 * SMALL_NW ? 4 : m <= 8 * SMALL_NW ? 8 : 16;
 
 }  // namespace
 
+template <typename T, typename S, bool PRE>
+SmallKernel<T, S> cycle_for(int sl, int rl, bool staged) {
+  return sl == 4   ? cycle_of<T, S, 4, 0, PRE>(rl, staged)
+         : sl == 8 ? cycle_of<T, S, 8, 0, PRE>(rl, staged)
+                   : cycle_of<T, S, 16, 0, PRE>(rl, staged);
+}
+
+// How far apart the blocks are that exchange rows (blocks of `rows`), or more
+// than any if a window does not fit.
+template <typename T>
+__global__ __launch_bounds__(SMALL_NT) void k_small_near(Csr A, int rows, int* far) {
+  __shared__ Window<T> win;
+  const int s0 = blockIdx.x * (rows / SELL_C);
+  window_build<SMALL_NT>(win, A, s0, min(rows / SELL_C, A.nslices - s0), win_chunks<T>());
+  int d = win.chunks > 0 ? 1 : SMALL_MAX_P;
+  for (int i = threadIdx.x; i < win.chunks; i += SMALL_NT) {
+    const int c = min(max(win.chunk[i], 0), A.nslices - 1);
+    d = max(d, abs(c / (rows / SELL_C) - (int)blockIdx.x));
+  }
+  atomicMax(far, d);
+}
+
+void small_near(const Csr& A, int sT, int rows, int blocks, int* far, hipStream_t s) {
+  if (sT == 8) hipLaunchKernelGGL(k_small_near<double>, dim3(blocks), dim3(SMALL_NT), 0, s, A, rows, far);
+  else hipLaunchKernelGGL(k_small_near<float>, dim3(blocks), dim3(SMALL_NT), 0, s, A, rows, far);
+}
+
 template <typename T, typename S>
 SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows, int blocks) {
   const int sl = slots_of(m);
-  if (ph == SMALL_CYCLE)
-    return sl == 4   ? cycle_of<T, S, 4, 0>(rows / WAVE, small_staged(blocks))
-           : sl == 8 ? cycle_of<T, S, 8, 0>(rows / WAVE, small_staged(blocks))
-                     : cycle_of<T, S, 16, 0>(rows / WAVE, small_staged(blocks));
+  if (ph == SMALL_CYCLE) return cycle_for<T, S, false>(sl, rows / WAVE, small_staged(blocks));
+  if (ph == SMALL_CYCLE_PRE) return cycle_for<T, S, true>(sl, rows / WAVE, small_staged(blocks));
   return sl == 4 ? phase_of<T, S, 4>(ph) : sl == 8 ? phase_of<T, S, 8>(ph) : phase_of<T, S, 16>(ph);
 }
 template SmallKernel<float, float> small_kernel<float, float>(SmallPhase, int, int, int);

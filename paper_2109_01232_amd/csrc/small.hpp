@@ -32,7 +32,37 @@ constexpr int SMALL_MAX_P = 256;                     // blocks
 constexpr int SMALL_GROUPS = 16;                     // of up to 16 blocks: an exchange's second stage
 constexpr size_t SMALL_WORDS_AT = (size_t)MAX_BLOCKS * 8;  // the words follow the partials of the cycle's set-up
 
-enum SmallPhase { SMALL_SPMV = 0, SMALL_GIVENS, SMALL_UPDATE, SMALL_NORM, SMALL_CYCLE };
+enum SmallPhase { SMALL_SPMV = 0, SMALL_GIVENS, SMALL_UPDATE, SMALL_NORM, SMALL_CYCLE, SMALL_CYCLE_PRE };
+
+// One SpMV step of a polynomial preconditioner's product form, in the inner
+// precision: vectors 0 (v_j) to 3, 4 none.
+template <typename T>
+struct PolyCoef {
+  T ay, aw, ax, at;  // y = ay*y + aw*W + ax*X + at*(A X)
+  T bw, bx, bt;      // d = bw*W + bx*X + bt*(A X)
+  int has_y, y_read, has_d, has_w;
+};
+template <typename T>
+__device__ __forceinline__ T poly_y(const PolyCoef<T>& cf, T wr, T xr, T t, T y) {
+  T yv = cf.aw * wr + cf.ax * xr + cf.at * t;
+  if (cf.y_read) yv += cf.ay * y;
+  return yv;
+}
+template <typename T>
+__device__ __forceinline__ T poly_d(const PolyCoef<T>& cf, T wr, T xr, T t) {
+  return cf.bw * wr + cf.bx * xr + cf.bt * t;
+}
+struct SmallStep {
+  double c[7];  // ay, aw, ax, at, bw, bx, bt
+  int w, d, has_y, y_read;
+};
+template <typename T>
+__host__ __device__ inline PolyCoef<T> poly_coef(const double* c, int has_y, int y_read, int d, int w) {
+  return {(T)c[0], (T)c[1], (T)c[2], (T)c[3], (T)c[4], (T)c[5], (T)c[6], has_y, y_read, d < 4, w < 4};
+}
+constexpr int SMALL_PRE_ROWS = 5;    // vectors of a block's rows a preconditioner's steps keep in LDS
+constexpr int SMALL_MAX_NEAR = 31;   // a wave looks at 63 neighbours
+constexpr size_t SMALL_PROG_AT = (size_t)MAX_BLOCKS * PART_COLS * 8 - 256 * sizeof(SmallStep);  // in the partials' place
 
 template <typename T, typename S>
 struct SmallArgs {
@@ -49,6 +79,11 @@ struct SmallArgs {
   unsigned int vals_lds;  // dynamic LDS of the cycle kernel: the block's rows of A, if they fit
   int rows, blocks;           // partition: rows per block (multiple of 64), blocks
   int j, kmax;
+  // SMALL_CYCLE_PRE: block Jacobi of block size bj (inverses as k_bj_apply's) or a polynomial of `steps` steps
+  int bj, steps, near;
+  const T* minv;
+  const SmallStep* prog;
+  unsigned long long *z, *z1;  // vectors as words
 };
 
 template <typename T>
@@ -65,6 +100,9 @@ template <typename T, typename S>
 using SmallKernel = void (*)(SmallArgs<T, S>);
 template <typename T, typename S>
 SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows, int blocks);
+
+// far: at least the distance of blocks that exchange rows, SMALL_MAX_P if a window does not fit
+void small_near(const Csr& A, int sT, int rows, int blocks, int* far, hipStream_t s);
 
 // words of the partial sums
 size_t small_words(int blocks, int sT);
