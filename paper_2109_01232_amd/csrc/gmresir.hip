@@ -58,7 +58,7 @@ constexpr int MAX_GRID = 1024;  // <= MAX_BLOCKS (partials per reduction)
 // to 2^21 rows, 2^20 in fp64): from a little past the limits of the one of
 // small.hip, the smallest sizes measured.  It is the faster one over all of
 // that range: solves of 263169 rows 88.5 -> 41.8 ms, 27-point of 1030301 24.8
-// -> 18.7, of 2^21 51.0 -> 44.9; fp64 136900 rows 59.7 -> 34.7, 1030301 50.7 -> 40.0.
+// -> 18.7, of 2^21 50.3 -> 42.9; fp64 136900 rows 59.7 -> 34.7, 1030301 50.7 -> 40.0.
 int64_t mid_min_n(int m, int sT) { return (sT == 4 && m <= 56 ? 1 << 18 : 1 << 17) + 1024; }
 constexpr int64_t GRAPH_MAX_N = 1 << 18;  // cycles of smaller systems run as HIP graphs
 constexpr size_t ALIGN = 256;
@@ -1056,7 +1056,7 @@ struct Ctx {
     // ortho 1 reads the basis twice an iteration: faster than three times in
     // part past 2^20 rows (1157625: 23.1, 24.2 ms; 512000: 13.1, 10.2)
     if (L.ls && n > 1 << 20) return;
-    mid_k = mid_kernel<T, S>(A->nslices);
+    mid_k = mid_kernel<T, S>(A->nslices, A->sell_wide);
     if (!mid_k.k) return;
     small_clear(words(), mid_words(), stream);
     mid_fits(Ain, mid_k.chunks, &st.hdr->wide, stream);  // read with the first residual

@@ -19,8 +19,8 @@
 // 5.6 TB/s), by the vector units and LDS barriers where most are resident.
 // Whole solves to 1e-12, GMRES(50), against one kernel per operation: fp32
 // 5-point 513^2 88.5 -> 41.8 ms, 600^2 98.8 -> 53.2, 27-point 80^3 15.8 -> 10.3,
-// 101^3 24.8 -> 18.7, 128^3 51.0 -> 44.9; bf16 basis 80^3 17.3 -> 11.9, 128^3
-// 42.2 -> 38.8; fp64 7-point 52^3 28.6 -> 16.1, 27-point 101^3 50.7 -> 40.0.
+// 101^3 24.8 -> 18.7, 128^3 50.3 -> 42.9; bf16 basis 80^3 17.3 -> 11.9, 128^3
+// 42.5 -> 37.2; fp64 7-point 52^3 28.6 -> 16.1, 27-point 101^3 50.7 -> 40.0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -160,7 +160,7 @@ typedef WindowMap<MID_CHUNKS, MID_PAIRS, MID_SLICES> MidWindow;
 // register index: unrolled, the sweeps' code outgrew the instruction cache
 // and their registers spilled; vectors of 32 because the compiler keeps ones
 // of 8 and 10 in scratch memory, 3x slower).  At most STEPS steps per block.
-template <typename T, typename S, int QR, int STEPS>
+template <typename T, typename S, int QR, int STEPS, int U>
 __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int NS = MID_SLOTS - QR;  // columns of a wave read from memory at most
@@ -321,18 +321,18 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
     bool lost = false;
     // x = v_j = round(w'' / ||w''||) into the window, then w = A x slice by
     // slice; the last wave makes the Givens step of j - 1 first
-    constexpr int U = 8;
-    for (int c0 = wid; c0 < win.chunks; c0 += U * MID_NW) {
-      T x[U];
+    constexpr int LOADS = 8;
+    for (int c0 = wid; c0 < win.chunks; c0 += LOADS * MID_NW) {
+      T x[LOADS];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < LOADS; ++u) {
         const int c = c0 + MID_NW * u;
         const int r = win.chunk[c < win.chunks ? c : c0] * SELL_C + lane;
         x[u] = load_shared(a.wtmp + (r >= 0 && r < n ? r : r0));
         if (r < 0 || r >= n) x[u] = T(0);
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int u = 0; u < LOADS; ++u)
         if (c0 + MID_NW * u < win.chunks) s_x[(c0 + MID_NW * u) * SELL_C + lane] = Basis<S, T>::round(x[u] * inv);
     }
     lds_barrier();
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
       s = __builtin_amdgcn_readfirstlane(s);
       if (s >= sl1 - sl0) break;
       const int i = s * SELL_C + lane, r = r0 + i;
-      const T y = window_row(win, s_x, vals + win.pair[s] * SELL_C, s, lane);
+      const T y = window_row<T, U>(win, s_x, vals + win.pair[s] * SELL_C, s, lane);
       if (r < n) Basis<S, T>::store(a.V + (size_t)j * a.ldv + r, own[i]);
       s_y[i] = r < n ? y : T(0);
     }
@@ -445,8 +445,10 @@ size_t mid_words() { return 2 * MID_SUMS + MID_NORM; }
 
 // 120 or 128 registers of a lane hold basis columns: 4 QR STEPS, so the fewer
 // steps a block has the more columns stay.  A step has 4 slices of fp32, 8 of
-// bf16, 2 of fp64.
-template <typename T, typename S>
+// bf16, 2 of fp64.  U: entries of a row loaded together (27-point 128^3 44.5
+// -> 43.2 ms with 14 instead of 9, bf16 basis 39.5 -> 37.8; 27 spills registers;
+// both in one kernel, chosen per slice, 7-point 90^3 43.9 -> 52.0; fp64 equal).
+template <typename T, typename S, int U>
 static MidKernel<T, S> mid_of(int64_t nslices) {
   constexpr int PER = V4<S>::RPL;
   const int64_t s = (nslices + MID_P - 1) / MID_P;  // slices of a block
@@ -459,26 +461,26 @@ static MidKernel<T, S> mid_of(int64_t nslices) {
   };
   if (s > MID_SLICES || s > 32 * PER) return {nullptr, 0, 0};
   if constexpr (PER > 2)  // fp64: the smallest system has nine slices a block
-    if (s <= 4 * PER) return of(k_mid_cycle<T, S, 8, 4>, 4);
-  if (s <= 5 * PER) return of(k_mid_cycle<T, S, 6, 5>, 5);
-  if (s <= 6 * PER) return of(k_mid_cycle<T, S, 5, 6>, 6);
-  if (s <= 8 * PER) return of(k_mid_cycle<T, S, 4, 8>, 8);
-  if (s <= 10 * PER) return of(k_mid_cycle<T, S, 3, 10>, 10);
-  if (s <= 16 * PER) return of(k_mid_cycle<T, S, 2, 16>, 16);
-  if constexpr (PER < 8) return of(k_mid_cycle<T, S, 1, 32>, 32);
+    if (s <= 4 * PER) return of(k_mid_cycle<T, S, 8, 4, U>, 4);
+  if (s <= 5 * PER) return of(k_mid_cycle<T, S, 6, 5, U>, 5);
+  if (s <= 6 * PER) return of(k_mid_cycle<T, S, 5, 6, U>, 6);
+  if (s <= 8 * PER) return of(k_mid_cycle<T, S, 4, 8, U>, 8);
+  if (s <= 10 * PER) return of(k_mid_cycle<T, S, 3, 10, U>, 10);
+  if (s <= 16 * PER) return of(k_mid_cycle<T, S, 2, 16, U>, 16);
+  if constexpr (PER < 8) return of(k_mid_cycle<T, S, 1, 32, U>, 32);
   return {nullptr, 0, 0};
 }
 template <>
-MidKernel<float, float> mid_kernel<float, float>(int64_t nslices) {
-  return mid_of<float, float>(nslices);
+MidKernel<float, float> mid_kernel<float, float>(int64_t nslices, bool wide) {
+  return wide ? mid_of<float, float, 14>(nslices) : mid_of<float, float, 9>(nslices);
 }
 template <>
-MidKernel<float, bf16_t> mid_kernel<float, bf16_t>(int64_t nslices) {
-  return mid_of<float, bf16_t>(nslices);
+MidKernel<float, bf16_t> mid_kernel<float, bf16_t>(int64_t nslices, bool wide) {
+  return wide ? mid_of<float, bf16_t, 14>(nslices) : mid_of<float, bf16_t, 9>(nslices);
 }
 template <>
-MidKernel<double, double> mid_kernel<double, double>(int64_t nslices) {
-  return mid_of<double, double>(nslices);
+MidKernel<double, double> mid_kernel<double, double>(int64_t nslices, bool) {
+  return mid_of<double, double, 9>(nslices);
 }
 
 }  // namespace gir

@@ -124,13 +124,13 @@ struct MidKernel {
 // sets *wide if a block's window does not fit
 void mid_fits(const Csr& A, int chunks, int* wide, hipStream_t s);
 template <typename T, typename S>
-MidKernel<T, S> mid_kernel(int64_t nslices);
+MidKernel<T, S> mid_kernel(int64_t nslices, bool wide);  // wide: slices of more than 9 entries a row
 template <>
-MidKernel<float, float> mid_kernel<float, float>(int64_t nslices);
+MidKernel<float, float> mid_kernel<float, float>(int64_t nslices, bool wide);
 template <>
-MidKernel<float, bf16_t> mid_kernel<float, bf16_t>(int64_t nslices);
+MidKernel<float, bf16_t> mid_kernel<float, bf16_t>(int64_t nslices, bool wide);
 template <>
-MidKernel<double, double> mid_kernel<double, double>(int64_t nslices);
+MidKernel<double, double> mid_kernel<double, double>(int64_t nslices, bool wide);
 size_t mid_words();
 
 }  // namespace gir

@@ -96,11 +96,10 @@ __device__ __forceinline__ void window_build(W_& W, const Csr& A, int s0, int ns
 }
 
 // Row sums of slice s from the window, in the order of sell_row; vals: the
-// slice's values (LDS or memory), 64 per entry.
-template <typename T, typename W_>
+// slice's values (LDS or memory), 64 per entry; U entries' loads go out together.
+template <typename T, int U = 9, typename W_>
 __device__ __forceinline__ T window_row(const W_& W, const T* x, const T* vals, int s, int lane) {
 #pragma clang fp contract(off)
-  constexpr int U = 9;
   const int p0 = W.pair[s], K = W.pair[s + 1] - p0;
   T sum = T(0);
   for (int k0 = 0; k0 < K; k0 += U) {
