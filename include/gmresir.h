@@ -190,8 +190,11 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    How a cycle is launched (profile = 0) depends on the system's size.  Where
    the basis fits the registers of the GPU's compute units (layout 3, restart
    <= 112; up to 262144 rows in fp32 and 131072 in fp64 at restart 50) it is one
-   cooperative kernel, whose blocks wait for each other inside it; HIP errors
-   when one of them does not answer for a minute.  With a preconditioner that
+   cooperative kernel, whose blocks wait for each other inside it.  If they are
+   not all on the GPU within 0.1 s of each other (other streams or processes
+   hold compute units), that cycle and the solve's later ones are launched as
+   with profile = 1; a block that falls silent for a minute later is an error
+   (HIP).  With a preconditioner that
    asks for a block size dividing 64 or poly_prec 0, and for rows that exchange
    values to lie at most 31 of the kernel's blocks apart.  So it is, with only
    the first columns of the basis in registers, for larger systems without a

@@ -80,6 +80,12 @@ struct Unit<double> {
 
 enum : int32_t { F_DONE = 1, F_BREAKDOWN = 2, F_NUMERIC = 4, F_STOPPED = 8 };
 
+// Why the blocks of a cycle kernel gave up (bits of StateHdr::lost, set by the
+// first one to give up): not all of them were on the GPU when it began, and
+// nothing that another launch of the cycle reads has changed; or one fell silent
+// later.
+enum : int32_t { LOST_ABSENT = 1, LOST_SILENT = 2 };
+
 struct StateHdr {
   double beta;      // ||b||_2 (fp64)
   double gamma;     // ||r||_2 of the current outer residual (fp64)
@@ -94,8 +100,8 @@ struct StateHdr {
   int32_t flags;        // F_* of the current cycle
   int32_t cycle_k;      // k and flags of the last finished cycle (kept across
   int32_t cycle_flags;  // the reset a new cycle start does)
-  int32_t lost;         // an exchange between the blocks of a cycle kernel timed out
-  int32_t wide;         // a block's window of x does not fit the cycle kernel of mid.hip
+  int32_t lost;         // LOST_*: an exchange between the blocks of a cycle kernel timed out
+  int32_t wide;         // of a cycle kernel's partition, see mid_fits and small_near
   int32_t pad;
   uint32_t spare[8];
 };

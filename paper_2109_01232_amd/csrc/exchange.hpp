@@ -7,10 +7,21 @@
 
 namespace gir {
 
-// a poll gives up after this many ticks of the 100 MHz clock (60 s: longer than
-// other work on the GPU keeps a block waiting): every block then leaves the
-// kernel and the solve reports an error
-constexpr long long POLL_TICKS = 6000000000ll;
+// A wait gives up after this many looks, of 0.5 to 1 us each.  Until every block
+// has taken part in one exchange some may not be on the GPU at all: other work
+// holds their compute units, or another process's cycle kernel that waits for
+// its own blocks.  That wait is short (0.1 s), and the host then has the cycle
+// made by kernels whose blocks need not run together.  A block that was there
+// and falls silent for a minute is an error.  (Looks, not the clock: read
+// as well, it cost the small cycles 3-5 %.)
+constexpr int ARRIVE_LOOKS = 1 << 17, SILENT_LOOKS = 1 << 26;
+
+// What a wave needs to wait: the word by which a block that has given up tells
+// all others, and how many looks it takes.
+struct Wait {
+  const int32_t* lost;
+  int looks;
+};
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -133,18 +144,24 @@ __device__ __forceinline__ double word_value(const word_t* w, double) {
 }
 
 // Repeats load() (which loads and says whether this lane's tags are right)
-// until every lane's are; wave-uniform, false on time-out.
+// until every lane's are; wave-uniform, false on giving up.
 template <typename F>
-__device__ __forceinline__ bool poll(F load) {
-  long long t0 = 0;
-  for (int tries = 0;; ++tries) {
+__device__ __forceinline__ bool poll(const Wait& wt, F load) {
+  for (int looks = 1;; ++looks) {
     if (__all(load())) return true;
-    if ((tries & 255) == 255) {
-      const long long now = wall_clock64();
-      if (t0 == 0) t0 = now;
-      else if (now - t0 > POLL_TICKS) return false;
-    }
+    if ((looks & 255) == 0 &&
+        (looks >= wt.looks || __builtin_amdgcn_readfirstlane(
+                                  __hip_atomic_load(wt.lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))))
+      return false;
   }
+}
+
+// By one thread of a block that has given up, at the kernel's end.  A cycle that
+// cannot be made again is over.
+__device__ __forceinline__ void give_up(StateHdr* hd, int32_t why) {
+  const int32_t first = __hip_atomic_load(&hd->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (first == 0) (void)__hip_atomic_fetch_or(&hd->lost, why, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((first ? first : why) & LOST_SILENT) hd->flags = F_DONE | F_NUMERIC;
 }
 
 // ---------------------------------------------------------------------------
@@ -161,7 +178,7 @@ struct SmallShared {
   T g;       // rotated right-hand side, entry j
   T nrm2;    // ||w''||^2 of the step the Givens wave works on
   int flags;
-  int lost;  // a poll timed out
+  int lost;  // LOST_*: a wait of this block was given up
 };
 
 // Least-squares update of step j by one wave (see givens_tail): the column

@@ -1082,6 +1082,17 @@ struct Ctx {
     return true;
   }
 
+  // The blocks of a cycle kernel were not all on the GPU together: what they
+  // would have done is still to do, and from here on by kernels launched one by
+  // one.  The cycle's step count is 0, so nothing has been made of it.
+  bool cycle_to_repeat(const StateHdr& h) {
+    if (h.lost != LOST_ABSENT || !(mid_k.k || (small_R > 0 && small_coop))) return false;
+    mid_k.k = nullptr;
+    small_coop = false;
+    if (small_pre) small_R = 0;
+    return true;
+  }
+
   bool small_pre = false;  // with a preconditioner in the cycle kernel
   int small_far = 0;       // distance of blocks that exchange rows
 
@@ -1314,7 +1325,7 @@ struct Ctx {
     HIP_TRY(hipStreamSynchronize(stream));
     HIP_TRY(hipGetLastError());
     prof->commit(h->cycle_k);
-    if (h->lost) {
+    if (h->lost & LOST_SILENT) {
       set_error("the blocks of a cycle kernel did not all answer within its time limit");
       return GMRESIR_ERR_HIP;
     }
@@ -1430,6 +1441,7 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
         break;
       }
       if (int e = c.read_hdr(&H, hist && hist_n < hist_cap)) return e;
+      if (c.cycle_to_repeat(H)) continue;
       res->cycles += 1;
       const int kc = H.cycle_k;
       if (hist && hist_n < hist_cap && kc > 0) {
@@ -1458,6 +1470,7 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
     c.cast(c.r64);
     const double gamma_old = gamma;
     if (int e = c.read_hdr(&H, single && hist && hist_n < hist_cap)) return e;
+    if (c.cycle_to_repeat(H)) continue;
     if (single) {
       res->cycles += 1;
       const int kc = H.cycle_k;
@@ -1500,12 +1513,12 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
 // fp32 Arnoldi process of `steps` steps from the fp64 vector src (scaled to
 // unit norm in fp32); fills the header and the unrotated Hessenberg matrix.
 int arnoldi32(const gmresir_matrix* A, const double* src, int steps, char* ws, const Layout& L, hipStream_t stream,
-              StateHdr* H, std::vector<double>* hbar, std::vector<double>* hist) {
+              StateHdr* H, std::vector<double>* hbar, std::vector<double>* hist, bool together = true) {
   Prof prof;
   prof.stream = stream;
   Ctx<float, float> c(A, ws, L, stream, &prof);
   c.init(0.0, 0, 1.0);
-  c.small_init(true, false);
+  c.small_init(together, false);
   c.cast(src);
   c.cycle(steps);
   // the Hessenberg matrix and the history are copied on the stream before
@@ -1520,6 +1533,7 @@ int arnoldi32(const gmresir_matrix* A, const double* src, int steps, char* ws, c
     HIP_TRY(hipMemcpyAsync(hist->data(), c.st.hist, steps * sizeof(double), hipMemcpyDeviceToHost, stream));
   }
   if (int e = c.read_hdr(H)) return e;
+  if (c.cycle_to_repeat(*H)) return arnoldi32(A, src, steps, ws, L, stream, H, hbar, hist, false);
   return 0;
 }
 

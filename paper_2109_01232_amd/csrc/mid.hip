@@ -110,12 +110,12 @@ __device__ __forceinline__ void lds_barrier() {
 // Sum over the 16 lines from `lines` of their first nq values: lane l has
 // value l % 8.  False on time-out.
 template <typename T>
-__device__ __forceinline__ bool take(const word_t* lines, int nq, unsigned int tag, int lane, T& out) {
+__device__ __forceinline__ bool take(const Wait& wt, const word_t* lines, int nq, unsigned int tag, int lane, T& out) {
   constexpr int WV = small_words_per_value<T>();
   const int q = lane & 7;
   const word_t* p = lines + (lane >> 3) * LINE + WV * q;
   word_t w[2][WV];
-  const bool ok = poll([&] {
+  const bool ok = poll(wt, [&] {
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -137,19 +137,19 @@ __device__ __forceinline__ bool take(const word_t* lines, int nq, unsigned int t
 // ([256] lines): block 0 of every 16 sums its group's into `second` ([16]),
 // everyone sums those.
 template <typename T>
-__device__ __forceinline__ bool combine(word_t* first, word_t* second, int lb, bool leads, int nq, unsigned int tag,
-                                        int lane, T& out) {
+__device__ __forceinline__ bool combine(const Wait& wt, word_t* first, word_t* second, int lb, bool leads, int nq,
+                                        unsigned int tag, int lane, T& out) {
   constexpr int WV = small_words_per_value<T>();
   if (leads) {
     __builtin_amdgcn_s_sleep(WAIT_ONE);
     T s;
-    if (!take(first + (size_t)lb * LINE, nq, tag, lane, s)) return false;
+    if (!take(wt, first + (size_t)lb * LINE, nq, tag, lane, s)) return false;
     if (lane < nq) put_value(second + (size_t)(lb / MID_GROUP) * LINE + WV * lane, s, tag);
     __builtin_amdgcn_s_sleep(WAIT_ONE);
   } else {
     __builtin_amdgcn_s_sleep(WAIT_TWO);
   }
-  return take(second, nq, tag, lane, out);
+  return take(wt, second, nq, tag, lane, out);
 }
 
 // Slices of a block, and the map of its window of x (see window.hpp)
@@ -298,14 +298,15 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
     }
   };
   // the wave's column sums over all blocks: into h (every lane) and all[]
-  auto exchange = [&](word_t* words, unsigned int tag, int nq, T (&acc)[MID_SLOTS], T* all, T (&h)[MID_SLOTS]) {
+  auto exchange = [&](int looks, word_t* words, unsigned int tag, int nq, T (&acc)[MID_SLOTS], T* all,
+                      T (&h)[MID_SLOTS]) {
     word_t* first = words + (size_t)wid * MID_P * LINE;
     word_t* second = words + (size_t)MID_NW * MID_P * LINE + (size_t)wid * (MID_P / MID_GROUP) * LINE;
     const T v = lane_sums<MID_SLOTS>(acc);
     if (lane % (WAVE / MID_SLOTS) == 0 && lane / (WAVE / MID_SLOTS) < nq)
       put_value(first + (size_t)lb * LINE + WV * (lane / (WAVE / MID_SLOTS)), v, tag);
     T s = T(0);
-    const bool ok = nq == 0 || combine(first, second, lb, leads, nq, tag, lane, s);
+    const bool ok = nq == 0 || combine(Wait{&a.st.hdr->lost, looks}, first, second, lb, leads, nq, tag, lane, s);
     if (lane < nq) all[wid + MID_NW * lane] = s;
 #pragma unroll
     for (int q = 0; q < MID_SLOTS; ++q) h[q] = q < nq ? read_lane(s, q) : T(0);
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
     // column j is read back by other waves of the block
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (sh.flags & F_DONE) break;
+    if ((sh.flags & F_DONE) | sh.lost) break;  // one test: with a branch for each the compiler spills res
     if (threadIdx.x == 0) s_next = 0;
 #pragma unroll
     for (int q = 0; q < MID_SLOTS; ++q) h[q] = T(0);
@@ -382,21 +383,23 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
     }
     sweep(std::integral_constant<int, 0>{}, j + 1, h, acc);
     lds_barrier();  // the window gives way to the parts
-    lost = !exchange(h1w, tag, nq, acc, sh.h1[j & 1], h);
+    lost = !exchange(j == 0 ? ARRIVE_LOOKS : SILENT_LOOKS, h1w, tag, nq, acc, sh.h1[j & 1], h);
     sweep(std::integral_constant<int, 1>{}, j + 1, h, acc);
-    lost = !exchange(h2w, tag, nq, acc, sh.h2, h) || lost;
+    // a wave that has given up stays silent: no block passes this exchange then
+    const bool absent = lost && j == 0;
+    lost = !exchange(SILENT_LOOKS, h2w, tag, lost ? 0 : nq, acc, sh.h2, h) || lost;
     sweep(std::integral_constant<int, 2>{}, j + 1, h, acc);
     const T nrm = lane_sum<1>(acc[0]);
     if (lane == 0) {
       sh.red[wid] = nrm;
-      if (lost) sh.lost = 1;
+      if (lost) sh.lost = absent ? LOST_ABSENT : LOST_SILENT;
     }
     lds_barrier();
+    if (sh.lost) break;  // wtmp stays as it was: the cycle may be made again
     for (int i = threadIdx.x; i < rows; i += MID_NT) store_shared(a.wtmp + r0 + i, s_y[i]);
     // the rows are out before the norm says so
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (sh.lost) break;
     if (threadIdx.x == 0) {
       T t = sh.red[0];
 #pragma unroll
@@ -404,13 +407,13 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
       put_value(nw + (size_t)lb * LINE, t, tag);
     }
     T n2 = T(0);
-    lost = !combine(nw, nw + (size_t)MID_P * LINE, lb, leads && wid == 0, 1, tag, lane, n2);
+    lost = !combine(Wait{&a.st.hdr->lost, SILENT_LOOKS}, nw, nw + (size_t)MID_P * LINE, lb, leads && wid == 0, 1, tag, lane, n2);
     n2 = read_lane(n2, 0);
     asm volatile("" ::: "memory");  // the gathers below stay behind the exchange
     inv = T(1) / sqrt(n2);
     if (lane == 0) {
       if (wid == MID_NW - 1) sh.nrm2 = n2;
-      if (lost) sh.lost = 1;
+      if (lost) sh.lost = LOST_SILENT;
     }
     if (j + 1 >= a.kmax) {
       if (wid == MID_NW - 1 && !lost) small_givens<T>(a.st, sh, j, a.kmax, gin, stop_abs, check_stop, writer);
@@ -418,12 +421,7 @@ __global__ __launch_bounds__(MID_NT) void k_mid_cycle(SmallArgs<T, S> a) {
     }
   }
   __syncthreads();
-  if (sh.lost && threadIdx.x == 0) {
-    // every block gives up: the solve ends with an error
-    StateHdr* o = a.st.hdr;
-    o->lost = 1;
-    o->flags = F_DONE | F_NUMERIC;
-  }
+  if (sh.lost && threadIdx.x == 0) give_up(a.st.hdr, sh.lost);
 }
 
 // Tells in `wide` if a block's window needs more than `most` chunks.

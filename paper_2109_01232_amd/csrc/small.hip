@@ -45,13 +45,13 @@ __device__ __forceinline__ int groups_of(int P) { return 8 + max(0, min(8, P - 1
 // out, lane l: the sum of value l % W over `count` <= 16 lines, `stride` words
 // apart; values from nq on are not there.  False on time-out.
 template <typename T, int W>
-__device__ __forceinline__ bool take(const word_t* lines, int stride, int count, int nq, unsigned int tag, int lane,
-                                     T& out) {
+__device__ __forceinline__ bool take(const Wait& wt, const word_t* lines, int stride, int count, int nq,
+                                     unsigned int tag, int lane, T& out) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int NB = WAVE / W < 16 ? WAVE / W : 16, G = 16 / NB;
   const int q = lane % W, bl = lane / W;
   word_t w[G][WV];
-  const bool ok = poll([&] {
+  const bool ok = poll(wt, [&] {
     bool right = true;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -78,15 +78,15 @@ __device__ __forceinline__ bool take(const word_t* lines, int stride, int count,
 // behind them.  The cycle kernel's blocks share the first one; with `alone`
 // (single phases, every line is there) a wave does all of it in the same order.
 template <typename T, int W>
-__device__ __forceinline__ bool take_staged(word_t* lines, int line, int P, bool leader, bool alone, int nq,
-                                            unsigned int tag, int lane, T& out) {
+__device__ __forceinline__ bool take_staged(const Wait& wt, word_t* lines, int line, int P, bool leader, bool alone,
+                                            int nq, unsigned int tag, int lane, T& out) {
   constexpr int NB = WAVE / W < 16 ? WAVE / W : 16;
   if (alone) {
     T sum = T(0);
     for (int g = 0; g < groups_of(P); ++g) {
       const Group G(g, P);
       T s;
-      if (!take<T, W>(lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
+      if (!take<T, W>(wt, lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
       sum += lane / W == g % NB && lane % W < nq ? s : T(0);
     }
     out = lane_sum<W>(sum);
@@ -95,13 +95,13 @@ __device__ __forceinline__ bool take_staged(word_t* lines, int line, int P, bool
   if (leader) {
     const Group G(group_of(blockIdx.x), P);
     T s;
-    if (!take<T, W>(lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
+    if (!take<T, W>(wt, lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
     if (lane < nq) put_value(lines + (size_t)(P + G.g) * line + small_words_per_value<T>() * lane, s, tag);
     __builtin_amdgcn_s_sleep(WAIT_ONE);
   } else {
     __builtin_amdgcn_s_sleep(WAIT_TWO);
   }
-  return take<T, W>(lines + (size_t)P * line, line, groups_of(P), nq, tag, lane, out);
+  return take<T, W>(wt, lines + (size_t)P * line, line, groups_of(P), nq, tag, lane, out);
 }
 
 // the wave's sums of acc[q], q < nq: its columns' partial sums
@@ -118,8 +118,8 @@ __device__ __forceinline__ void publish(word_t* words, int P, int wid, int lane,
 // all[wid + 7 q].  SLOTS lanes take a line's values side by side, 64 / SLOTS
 // blocks at once; a pass has up to eight such loads in flight.
 template <typename T, int SLOTS, bool STAGED>
-__device__ __forceinline__ bool collect(word_t* words, int P, int wid, int lane, unsigned int tag, T (&out)[SLOTS],
-                                        T* all, int nq, bool alone = false) {
+__device__ __forceinline__ bool collect(const Wait& wt, word_t* words, int P, int wid, int lane, unsigned int tag,
+                                        T (&out)[SLOTS], T* all, int nq, bool alone = false) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int W = SLOTS, NB = WAVE / W;
   constexpr int G = 8 / WV;
@@ -127,12 +127,13 @@ __device__ __forceinline__ bool collect(word_t* words, int P, int wid, int lane,
   const word_t* p = line_of<T>(words, P, wid, 0) + WV * q;
   T sum = T(0);
   if constexpr (STAGED) {
-    if (!take_staged<T, W>(line_of<T>(words, P, wid, 0), LINE * WV, P, leads_group(blockIdx.x), alone, nq, tag, lane, sum))
+    if (!take_staged<T, W>(wt, line_of<T>(words, P, wid, 0), LINE * WV, P, leads_group(blockIdx.x), alone, nq, tag, lane,
+                           sum))
       return false;
   } else {
     for (int b0 = 0; b0 < P; b0 += NB * G) {
       word_t w[G][WV];
-      const bool ok = poll([&] {
+      const bool ok = poll(wt, [&] {
         bool right = true;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -165,16 +166,16 @@ __device__ __forceinline__ bool collect(word_t* words, int P, int wid, int lane,
 // one value a block, in a line of its own: the sum over the blocks
 // (past 64 blocks `leader`: this wave sums its group's for the others).
 template <typename T, bool STAGED>
-__device__ __forceinline__ bool collect_one(word_t* words, int P, int lane, unsigned int tag, T& out,
+__device__ __forceinline__ bool collect_one(const Wait& wt, word_t* words, int P, int lane, unsigned int tag, T& out,
                                             bool leader = false, bool alone = false) {
   constexpr int WV = small_words_per_value<T>();
   if constexpr (STAGED) {
     T s;
-    if (!take_staged<T, 1>(words, LINE, P, leader, alone, 1, tag, lane, s)) return false;
+    if (!take_staged<T, 1>(wt, words, LINE, P, leader, alone, 1, tag, lane, s)) return false;
     out = read_lane(s, 0);
   } else {
     word_t w[WV];
-    const bool ok = poll([&] {
+    const bool ok = poll(wt, [&] {
       bool all = true;
 #pragma unroll
       for (int h = 0; h < WV; ++h) w[h] = get_word(words + (unsigned)((lane < P ? lane : P - 1) * LINE + h));
@@ -190,15 +191,16 @@ __device__ __forceinline__ bool collect_one(word_t* words, int P, int lane, unsi
 
 // the same in the single phases
 template <typename T, int SLOTS>
-__device__ __forceinline__ bool collect_alone(word_t* words, int P, int wid, int lane, unsigned int tag, T (&out)[SLOTS],
-                                              T* all, int nq) {
-  return small_staged(P) ? collect<T, SLOTS, true>(words, P, wid, lane, tag, out, all, nq, true)
-                         : collect<T, SLOTS, false>(words, P, wid, lane, tag, out, all, nq);
+__device__ __forceinline__ bool collect_alone(const Wait& wt, word_t* words, int P, int wid, int lane, unsigned int tag,
+                                              T (&out)[SLOTS], T* all, int nq) {
+  return small_staged(P) ? collect<T, SLOTS, true>(wt, words, P, wid, lane, tag, out, all, nq, true)
+                         : collect<T, SLOTS, false>(wt, words, P, wid, lane, tag, out, all, nq);
 }
 template <typename T>
-__device__ __forceinline__ bool collect_one_alone(word_t* words, int P, int lane, unsigned int tag, T& out) {
-  return small_staged(P) ? collect_one<T, true>(words, P, lane, tag, out, false, true)
-                         : collect_one<T, false>(words, P, lane, tag, out);
+__device__ __forceinline__ bool collect_one_alone(const Wait& wt, word_t* words, int P, int lane, unsigned int tag,
+                                                  T& out) {
+  return small_staged(P) ? collect_one<T, true>(wt, words, P, lane, tag, out, false, true)
+                         : collect_one<T, false>(wt, words, P, lane, tag, out);
 }
 
 // A block's rows of V in memory (the single phases): column c, local row i, 0 past n.
@@ -302,8 +304,8 @@ __device__ __forceinline__ T small_updated(const T* part, T w, int rows, int i) 
 // are those of sell_row.  The norm's sum is polled behind the first round's
 // gathers, which are in flight meanwhile.
 template <typename T, typename S, int U, bool STAGED>
-__device__ __forceinline__ bool gather_row(const Csr& A, const word_t* x, unsigned int tag, word_t* norm, int P,
-                                           int r, int lane, int base, int K, bool& have_inv, T& inv, T& y) {
+__device__ __forceinline__ bool gather_row(const Wait& wt, const Csr& A, const word_t* x, unsigned int tag,
+                                           word_t* norm, int P, int r, int lane, int base, int K, bool& have_inv, T& inv, T& y) {
 #pragma clang fp contract(off)
   constexpr int WV = small_words_per_value<T>();
   const T* vals = (const T*)A.svals + base + lane;
@@ -336,11 +338,11 @@ __device__ __forceinline__ bool gather_row(const Csr& A, const word_t* x, unsign
     load();
     if (!have_inv) {
       T n2;
-      if (!collect_one<T, STAGED>(norm, P, lane, tag, n2)) return false;
+      if (!collect_one<T, STAGED>(wt, norm, P, lane, tag, n2)) return false;
       inv = T(1) / sqrt(n2);
       have_inv = true;
     }
-    if (!__all(right()) && !poll([&] {
+    if (!__all(right()) && !poll(wt, [&] {
           load();
           return right();
         }))
@@ -374,8 +376,8 @@ struct Window : WindowMap<win_chunks<T>(), 512, SMALL_MAX_RL> {
 // batch of loads.
 // PLAIN: the words' values as they are.
 template <typename T, typename S, bool STAGED, bool PLAIN = false>
-__device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n, unsigned int tag, word_t* norm,
-                                            int P, int wid, int lane, bool have_inv, T& inv) {
+__device__ __forceinline__ bool window_load(const Wait& wt, Window<T>& W, const word_t* x, int n, unsigned int tag,
+                                            word_t* norm, int P, int wid, int lane, bool have_inv, T& inv) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int G = 4;
   for (int c0 = wid; c0 < W.chunks; c0 += G * SMALL_NW) {
@@ -404,11 +406,11 @@ __device__ __forceinline__ bool window_load(Window<T>& W, const word_t* x, int n
     load();
     if (!PLAIN && !have_inv) {
       T n2;
-      if (!collect_one<T, STAGED>(norm, P, lane, tag, n2)) return false;
+      if (!collect_one<T, STAGED>(wt, norm, P, lane, tag, n2)) return false;
       inv = T(1) / sqrt(n2);
       have_inv = true;
     }
-    if (!__all(right()) && !poll([&] {
+    if (!__all(right()) && !poll(wt, [&] {
           load();
           return right();
         }))
@@ -490,7 +492,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     for (int i = 0; i < RL; ++i) V[q][i] = T(0);
   const bool writer = blockIdx.x == 0;
   // V[:, c]^T w of the wave's columns, summed over the blocks; then their part of V h
-  auto project = [&](word_t* words, unsigned int tag, int nq, T* all, T (&h)[SLOTS]) {
+  auto project = [&](const Wait& wt, word_t* words, unsigned int tag, int nq, T* all, T (&h)[SLOTS]) {
     T wv[RL], acc[SLOTS];
 #pragma unroll
     for (int i = 0; i < RL; ++i) wv[i] = s_w[lane + WAVE * i];
@@ -506,7 +508,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     if (nq > 0) {
       publish<T, SLOTS>(words, P, wid, lane, tag, acc, nq);
       __builtin_amdgcn_s_sleep(POLL_WAIT);
-      ok = collect<T, SLOTS, STAGED>(words, P, wid, lane, tag, h, all, nq);
+      ok = collect<T, SLOTS, STAGED>(wt, words, P, wid, lane, tag, h, all, nq);
     }
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
@@ -524,15 +526,17 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     for (int i = threadIdx.x; i < win.pair[RL] * SELL_C; i += SMALL_NT) s_vals[i] = vals[i];
   const int own = win.chunks > 0 ? win.own * SELL_C : 0;  // the block's rows in win.x
   __syncthreads();
-  // the vector with `tag` at x into the window; every other wave's done too
-  auto exchange_window = [&](word_t* x, unsigned int tag, int near) {
-    bool ok = true;
-    if (worker) {
-      ok = window_load<T, S, STAGED, true>(win, x, n, tag, nullptr, P, wid, lane, true, inv);
+  // the vector with `tag` at x into the window; every other wave's done too.
+  // A wave that has given up waits no more.
+  auto exchange_window = [&](const Wait& wt, word_t* x, unsigned int tag, int near, bool lost) {
+    bool ok = !lost;
+    if (lost) {
+    } else if (worker) {
+      ok = window_load<T, S, STAGED, true>(wt, win, x, n, tag, nullptr, P, wid, lane, true, inv);
     } else if (near > 0) {
       const int b = (int)blockIdx.x - near + lane;
       const bool there = lane <= 2 * near && b >= 0 && b < P;
-      ok = poll([&] { return !there || (unsigned int)get_word(x + (size_t)(there ? b : 0) * ROWS * WV) == tag; });
+      ok = poll(wt, [&] { return !there || (unsigned int)get_word(x + (size_t)(there ? b : 0) * ROWS * WV) == tag; });
     }
     __syncthreads();
     return ok;
@@ -541,16 +545,18 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
   for (;; ++j) {
     const unsigned int tag = a.tag + (unsigned int)j;
     const int nq = wid <= j ? (j - wid) / SMALL_NW + 1 : 0;
+    // until every block's sums of the first projection are in, some may not be there
+    const Wait wt{&a.st.hdr->lost, j == 0 ? ARRIVE_LOOKS : SILENT_LOOKS};
     T h[SLOTS];
     bool lost = false;
     // v_j = round(w'' / ||w''||) and w = A v_j
     __builtin_amdgcn_s_sleep(POLL_WAIT);
     if (worker) {
       if (win.chunks > 0)
-        lost = !window_load<T, S, STAGED>(win, a.x, n, tag - 1, nw, P, wid, lane, j == 0, inv);
+        lost = !window_load<T, S, STAGED>(wt, win, a.x, n, tag - 1, nw, P, wid, lane, j == 0, inv);
     } else if (j > 0) {
       T n2 = T(0);
-      lost = !collect_one<T, STAGED>(nw, P, lane, tag - 1, n2, leads_group(blockIdx.x));
+      lost = !collect_one<T, STAGED>(wt, nw, P, lane, tag - 1, n2, leads_group(blockIdx.x));
       if (lane == 0) sh.nrm2 = n2;
     }
     __syncthreads();
@@ -584,7 +590,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
       }
       if (a.bj > 0) {
         __syncthreads();
-        lost = !exchange_window(a.z, tag, 0) || lost;
+        lost = !exchange_window(wt, a.z, tag, 0, lost);
       }
       for (int k = 0; k < a.steps; ++k) {
         const SmallStep& ps = a.prog[k];
@@ -611,7 +617,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
             if (r < n) put_value(to + (size_t)r * WV, out, ptag);
           }
         __syncthreads();
-        lost = !exchange_window(to, ptag, a.near) || lost;
+        lost = !exchange_window(wt, to, ptag, a.near, lost);
       }
     }
     if (worker) {
@@ -626,10 +632,10 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
           } else {
             const int base = a.A.sptr[sl];
             const int K = (a.A.sptr[sl + 1] - base) / SELL_C;
-            lost = !gather_row<T, S, 5, STAGED>(a.A, a.x, tag - 1, nw, P, r, lane, base, K, have_inv, inv, y);
+            lost = !gather_row<T, S, 5, STAGED>(wt, a.A, a.x, tag - 1, nw, P, r, lane, base, K, have_inv, inv, y);
             if (!have_inv && !lost) {  // a slice without entries
               T n2 = T(0);
-              lost = !collect_one<T, STAGED>(nw, P, lane, tag - 1, n2);
+              lost = !collect_one<T, STAGED>(wt, nw, P, lane, tag - 1, n2);
               inv = T(1) / sqrt(n2);
               have_inv = true;
             }
@@ -650,19 +656,19 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
 #pragma unroll
             for (int i = 0; i < RL; ++i) V[q][i] = r0 / SELL_C + i < a.A.nslices ? win.x[own + lane + WAVE * i] : T(0);
       }
-      lost = !project(h1w, tag, nq, sh.h1[j & 1], h) || lost;
+      lost = !project(wt, h1w, tag, nq, sh.h1[j & 1], h) || lost;
     } else if (j > 0) {
       small_givens<T>(a.st, sh, j - 1, a.kmax, gin, stop_abs, check_stop, writer);
     }
-    if (lost && lane == 0) sh.lost = 1;
+    if (lost && lane == 0) sh.lost = j == 0 ? LOST_ABSENT : LOST_SILENT;
     __syncthreads();
     if ((sh.flags & F_DONE) || sh.lost) break;
     // w' = w - V h1, h2 = V^T w'
     if (worker)
       for (int i = wid * WAVE + lane; i < ROWS; i += SMALL_NW * WAVE) s_w[i] = small_updated(&s_part[0][0], s_w[i], ROWS, i);
     __syncthreads();
-    if (worker) lost = !project(h2w, tag, nq, sh.h2, h);
-    if (lost && lane == 0) sh.lost = 1;
+    if (worker) lost = !project(Wait{wt.lost, SILENT_LOOKS}, h2w, tag, nq, sh.h2, h);
+    if (lost && lane == 0) sh.lost = LOST_SILENT;
     __syncthreads();
     if (sh.lost) break;
     // w'' = w' - V h2 for the other blocks, and its norm
@@ -689,10 +695,10 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     if (j + 1 >= a.kmax) {
       if (!worker) {
         T n2 = T(0);
-        lost = !collect_one<T, STAGED>(nw, P, lane, tag, n2, leads_group(blockIdx.x));
+        lost = !collect_one<T, STAGED>(Wait{wt.lost, SILENT_LOOKS}, nw, P, lane, tag, n2, leads_group(blockIdx.x));
         if (lane == 0) {
           sh.nrm2 = n2;
-          if (lost) sh.lost = 1;
+          if (lost) sh.lost = LOST_SILENT;
         }
         if (!lost) small_givens<T>(a.st, sh, j, a.kmax, gin, stop_abs, check_stop, writer);
       }
@@ -700,12 +706,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_cycle(SmallArgs<T, S> a) {
     }
   }
   __syncthreads();
-  if (sh.lost && threadIdx.x == 0) {
-    // every block gives up: the solve ends with an error
-    StateHdr* o = a.st.hdr;
-    o->lost = 1;
-    o->flags = F_DONE | F_NUMERIC;
-  }
+  if (sh.lost && threadIdx.x == 0) give_up(a.st.hdr, sh.lost);
 }
 
 // ---------------------------------------------------------------------------
@@ -732,6 +733,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
   const unsigned int tag = a.tag + (unsigned int)j;
   const int nq = worker && wid <= j ? (j - wid) / SMALL_NW + 1 : 0;
   const VGlobal<T, S> V{a.V + r0, a.ldv, n - r0};
+  const Wait wt{&a.st.hdr->lost, SILENT_LOOKS};
   T h[SLOTS];
   bool lost = false;
   if constexpr (PH == SMALL_GIVENS) {
@@ -739,12 +741,12 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     const StateHdr* hd = a.st.hdr;
     if (worker) {
       if (nq > 0) {
-        lost = !collect_alone<T, SLOTS>(h1w, P, wid, lane, tag, h, sh.h1[j & 1], nq);
-        lost = !collect_alone<T, SLOTS>(h2w, P, wid, lane, tag, h, sh.h2, nq) || lost;
+        lost = !collect_alone<T, SLOTS>(wt, h1w, P, wid, lane, tag, h, sh.h1[j & 1], nq);
+        lost = !collect_alone<T, SLOTS>(wt, h2w, P, wid, lane, tag, h, sh.h2, nq) || lost;
       }
     } else {
       T n2 = T(0);
-      lost = !collect_one_alone(nw, P, lane, tag, n2);
+      lost = !collect_one_alone(wt, nw, P, lane, tag, n2);
       for (int i = lane; i < j; i += WAVE) {
         sh.cs[i] = (T)a.st.cs[i];
         sh.sn[i] = (T)a.st.sn[i];
@@ -762,7 +764,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     T inv = (T)a.st.hdr->inv_h;
     if (j > 0) {
       T n2 = T(0);
-      lost = !collect_one_alone(nw, P, lane, tag - 1, n2);
+      lost = !collect_one_alone(wt, nw, P, lane, tag - 1, n2);
       inv = T(1) / sqrt(n2);
     }
     const XScaled<T, S> xs{a.wtmp, inv};
@@ -790,7 +792,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     constexpr bool FIRST = PH == SMALL_UPDATE;
     const T* in = FIRST ? a.w1 : a.w2;
     T* out = FIRST ? a.w2 : a.wtmp;
-    if (nq > 0) lost = !collect_alone<T, SLOTS>(FIRST ? h1w : h2w, P, wid, lane, tag, h, sh.h2, nq);
+    if (nq > 0) lost = !collect_alone<T, SLOTS>(wt, FIRST ? h1w : h2w, P, wid, lane, tag, h, sh.h2, nq);
     if (worker) small_partial<T, SLOTS>(part, V, h, rows, j, wid, lane);
     __syncthreads();
     T nrm = T(0);
@@ -818,7 +820,7 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     }
   }
   if (lost && lane == 0) {
-    a.st.hdr->lost = 1;
+    a.st.hdr->lost = LOST_SILENT;
     a.st.hdr->flags = F_DONE | F_NUMERIC;
   }
 }
