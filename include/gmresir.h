@@ -109,7 +109,8 @@ typedef struct {
                           2022): one reduction and two sweeps of the basis per iteration, results
                           equal to CGS2's in exact arithmetic.  1 needs basis_prec = inner_prec
                           (no BF16) and restart <= 128.  Where a cycle is one kernel (see
-                          gmresir_solve) it makes the two passes of 0, which are faster there. */
+                          gmresir_solve) it makes the two passes of 0, which are faster there; so do
+                          the kernels launched one by one up to 65536 rows (32768 in fp64). */
 } gmresir_params;
 
 typedef struct {
@@ -203,8 +204,9 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    rows reach fit a compute unit's LDS.  Other systems of n <= 2^18 record the
    kernels of a cycle once as a HIP graph, replayed for every later cycle of the
    same length.  With profile = 1 and in gmresir_solve_noalloc every kernel is
-   launched directly; the bits are the same, but for the larger systems and with
-   a preconditioner: there the cycle kernel sums in another order. */
+   launched directly; the bits are the same, but for the larger systems, with a
+   preconditioner, and with ortho 1 past 65536 rows (32768 in fp64): there the
+   cycle kernel sums in another order. */
 int gmresir_solve(const gmresir_matrix* A, const double* b, double* x, const gmresir_params* p,
                   const double* poly_roots_host, void* ws, size_t ws_bytes, gmresir_result* res_host,
                   double* hist_host, int64_t hist_cap, void* stream);

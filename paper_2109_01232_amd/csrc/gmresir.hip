@@ -1112,6 +1112,14 @@ struct Ctx {
     if (small_R == 0) return;
     small_P = (n + small_R - 1) / small_R;
     small_coop = coop && !prof->on;
+    // Launched one by one the two passes are the faster ones only while an
+    // iteration is bound by its launches (one reduction, two passes: fp32 22500
+    // rows 24.7, 21.5 us, 62500 25.9, 25.6, 250000 30.2, 39.8; fp64 22500 26.6,
+    // 25.8, 62500 28.8, 32.9).
+    if (L.ls && !small_coop && n > (sizeof(T) == 8 ? 1 << 15 : 1 << 16)) {
+      small_R = 0;
+      return;
+    }
     if (pre) {
       const size_t rows = (size_t)SMALL_PRE_ROWS * small_R * sizeof(T);
       if (!small_coop || poly32 || (L.bj > 0 && WAVE % L.bj != 0) ||
@@ -1175,12 +1183,12 @@ struct Ctx {
                      : ph == SMALL_SPMV ? spmv_bytes() + sT() * n * 2 + sS() * n * (j + 1)
                                         : sT() * n * 2 + sS() * n * (j + 1);
     prof->tag = j;
-    prof->early = false;
+    prof->early = launch && ph == SMALL_SPMV;  // the stop is decided beside it
     if (!launch) {
       prof->pend.push_back({cat, b, j, false, nullptr, nullptr});
       return;
     }
-    const int g = ph == SMALL_GIVENS ? 1 : small_P;
+    const int g = ph == SMALL_GIVENS ? 1 : ph == SMALL_SPMV && j > 0 ? small_P + 1 : small_P;
     prof->launch(cat, b, small_kernel<T, S>(ph, L.m, small_R, small_P), dim3(g), dim3(SMALL_NT),
                  small_phase_lds(small_R, (int)sizeof(T)), stream, small_args(j, kmax));
   }
@@ -1213,9 +1221,12 @@ struct Ctx {
       for (size_t k = 0; poly_on && k < prog.size(); ++k)
         prof->pend.push_back({GMRESIR_CAT_POLY, spmv_bytes() + sT() * n * 3, j, true, nullptr, nullptr});
     }
-    for (int j = 0; j < kmax; ++j)
-      for (SmallPhase ph : {SMALL_SPMV, SMALL_UPDATE, SMALL_NORM, SMALL_GIVENS}) small_phase(ph, j, kmax, !launched);
+    for (int j = 0; j < kmax; ++j) {
+      for (SmallPhase ph : {SMALL_SPMV, SMALL_UPDATE, SMALL_NORM}) small_phase(ph, j, kmax, !launched);
+      if (launched || j + 1 == kmax) small_phase(SMALL_GIVENS, j, kmax, !launched);  // the others beside the SpMV
+    }
     prof->tag = -1;
+    prof->early = false;
     small_tag += SMALL_MAX_M + 2;
   }
 

@@ -42,55 +42,102 @@ __device__ __forceinline__ int group_of(int b) { return b % 8 + 8 * (b / 128); }
 __device__ __forceinline__ bool leads_group(int b) { return b / 8 % 16 == 0; }
 __device__ __forceinline__ int groups_of(int P) { return 8 + max(0, min(8, P - 128)); }
 
-// out, lane l: the sum of value l % W over `count` <= 16 lines, `stride` words
-// apart; values from nq on are not there.  False on time-out.
-template <typename T, int W>
-__device__ __forceinline__ bool take(const Wait& wt, const word_t* lines, int stride, int count, int nq,
-                                     unsigned int tag, int lane, T& out) {
-  constexpr int WV = small_words_per_value<T>();
-  constexpr int NB = WAVE / W < 16 ? WAVE / W : 16, G = 16 / NB;
-  const int q = lane % W, bl = lane / W;
+// The single phases read what an earlier launch has written: every word is
+// there, and the loads go through the caches (past them every block fetches
+// every line from memory: an iteration of 62500 rows 27.5 instead of 25.6 us, of
+// 22500 26.7 instead of 21.7).
+template <bool ALONE>
+__device__ __forceinline__ word_t look_at(const word_t* p) {
+  if constexpr (ALONE) return *p;
+  else return get_word(p);
+}
+template <bool ALONE, typename F>
+__device__ __forceinline__ bool wait_for(const Wait& wt, F load) {
+  if constexpr (ALONE) return __all(load());
+  else return poll(wt, load);
+}
+
+// The words of `count` <= 16 lines, `stride` words apart, as a lane sees them:
+// value lane % W of the lines lane / W + NB g.
+template <typename T, int W, bool ALONE = false>
+struct Lines {
+  static constexpr int WV = small_words_per_value<T>();
+  static constexpr int NB = WAVE / W < 16 ? WAVE / W : 16, G = 16 / NB;
   word_t w[G][WV];
-  const bool ok = poll(wt, [&] {
-    bool right = true;
+  __device__ __forceinline__ void load(const word_t* lines, int stride, int count, int lane) {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const int b = NB * g + bl;
+      const int b = NB * g + lane / W;
 #pragma unroll
-      for (int h = 0; h < WV; ++h) w[g][h] = get_word(lines + (unsigned)((b < count ? b : 0) * stride + WV * q + h));
+      for (int h = 0; h < WV; ++h) w[g][h] = look_at<ALONE>(lines + (unsigned)((b < count ? b : 0) * stride + WV * (lane % W) + h));
     }
+  }
+  // the tags are right; values from nq on are not there
+  __device__ __forceinline__ bool right(int count, int nq, unsigned int tag, int lane) const {
+    bool ok = true;
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int h = 0; h < WV; ++h)
-        right = right && ((unsigned int)w[g][h] == tag || q >= nq || NB * g + bl >= count);
-    return right;
+        ok = ok && ((unsigned int)w[g][h] == tag || lane % W >= nq || NB * g + lane / W >= count);
+    return ok;
+  }
+  // lane l: the sum of value l % W
+  __device__ __forceinline__ T sum(int count, int nq, int lane) const {
+    const int bl = lane / W;
+    T s = T(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) s += NB * g + bl < count && bl < NB && lane % W < nq ? word_value(w[g], T(0)) : T(0);
+    return lane_sum<W>(s);
+  }
+};
+
+// out, lane l: the sum of value l % W over the lines.  False on giving up.
+template <typename T, int W>
+__device__ __forceinline__ bool take(const Wait& wt, const word_t* lines, int stride, int count, int nq,
+                                     unsigned int tag, int lane, T& out) {
+  Lines<T, W> k;
+  const bool ok = poll(wt, [&] {
+    k.load(lines, stride, count, lane);
+    return k.right(count, nq, tag, lane);
   });
   if (!ok) return false;
-  T s = T(0);
-#pragma unroll
-  for (int g = 0; g < G; ++g) s += NB * g + bl < count && bl < NB && q < nq ? word_value(w[g], T(0)) : T(0);
-  out = lane_sum<W>(s);
+  out = k.sum(count, nq, lane);
   return true;
 }
 
 // The two stages over P lines from `lines`, `line` words each, the groups'
-// behind them.  The cycle kernel's blocks share the first one; with `alone`
-// (single phases, every line is there) a wave does all of it in the same order.
-template <typename T, int W>
-__device__ __forceinline__ bool take_staged(const Wait& wt, word_t* lines, int line, int P, bool leader, bool alone,
-                                            int nq, unsigned int tag, int lane, T& out) {
-  constexpr int NB = WAVE / W < 16 ? WAVE / W : 16;
-  if (alone) {
+// behind them.  The cycle kernel's blocks share the first one; ALONE (the single
+// phases) a wave does all of it in the same order, eight groups' loads in flight
+// together (group after group an iteration of 62500 rows launched phase by phase
+// took 60 us instead of 30; the general kernels' 31).
+template <typename T, int W, bool ALONE>
+__device__ __forceinline__ bool take_staged(const Wait& wt, word_t* lines, int line, int P, bool leader, int nq,
+                                            unsigned int tag, int lane, T& out) {
+  if constexpr (ALONE) {
+    typedef Lines<T, W, true> Group_;
+    constexpr int NB = Group_::NB, AT = 32 / (Group_::G * Group_::WV) < 8 ? 32 / (Group_::G * Group_::WV) : 8;
+    const int groups = groups_of(P);
+    bool right = true;
     T sum = T(0);
-    for (int g = 0; g < groups_of(P); ++g) {
-      const Group G(g, P);
-      T s;
-      if (!take<T, W>(wt, lines + (size_t)G.first * line, 8 * line, G.count, nq, tag, lane, s)) return false;
-      sum += lane / W == g % NB && lane % W < nq ? s : T(0);
+    for (int g0 = 0; g0 < groups; g0 += AT) {
+      Group_ k[AT];
+      int count[AT];
+#pragma unroll
+      for (int i = 0; i < AT; ++i) {
+        const Group G(g0 + i < groups ? g0 + i : 0, P);
+        count[i] = g0 + i < groups ? G.count : 0;
+        k[i].load(lines + (size_t)G.first * line, 8 * line, G.count, lane);
+      }
+#pragma unroll
+      for (int i = 0; i < AT; ++i) {
+        right = right && k[i].right(count[i], nq, tag, lane);
+        const T s = k[i].sum(count[i], nq, lane);
+        if (g0 + i < groups) sum += lane / W == (g0 + i) % NB && lane % W < nq ? s : T(0);
+      }
     }
     out = lane_sum<W>(sum);
-    return true;
+    return __all(right);
   }
   if (leader) {
     const Group G(group_of(blockIdx.x), P);
@@ -117,9 +164,9 @@ __device__ __forceinline__ void publish(word_t* words, int P, int wid, int lane,
 // out[q], q < nq: the sums over the P blocks, in every lane, and kept in
 // all[wid + 7 q].  SLOTS lanes take a line's values side by side, 64 / SLOTS
 // blocks at once; a pass has up to eight such loads in flight.
-template <typename T, int SLOTS, bool STAGED>
+template <typename T, int SLOTS, bool STAGED, bool ALONE = false>
 __device__ __forceinline__ bool collect(const Wait& wt, word_t* words, int P, int wid, int lane, unsigned int tag,
-                                        T (&out)[SLOTS], T* all, int nq, bool alone = false) {
+                                        T (&out)[SLOTS], T* all, int nq) {
   constexpr int WV = small_words_per_value<T>();
   constexpr int W = SLOTS, NB = WAVE / W;
   constexpr int G = 8 / WV;
@@ -127,20 +174,20 @@ __device__ __forceinline__ bool collect(const Wait& wt, word_t* words, int P, in
   const word_t* p = line_of<T>(words, P, wid, 0) + WV * q;
   T sum = T(0);
   if constexpr (STAGED) {
-    if (!take_staged<T, W>(wt, line_of<T>(words, P, wid, 0), LINE * WV, P, leads_group(blockIdx.x), alone, nq, tag, lane,
-                           sum))
+    if (!take_staged<T, W, ALONE>(wt, line_of<T>(words, P, wid, 0), LINE * WV, P, leads_group(blockIdx.x), nq, tag, lane,
+                                  sum))
       return false;
   } else {
     for (int b0 = 0; b0 < P; b0 += NB * G) {
       word_t w[G][WV];
-      const bool ok = poll(wt, [&] {
+      const bool ok = wait_for<ALONE>(wt, [&] {
         bool right = true;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           const int b = b0 + NB * g + bl;
           if (NB * g + b0 < P)
 #pragma unroll
-            for (int h = 0; h < WV; ++h) w[g][h] = get_word(p + (unsigned)((b < P ? b : P - 1) * LINE * WV + h));
+            for (int h = 0; h < WV; ++h) w[g][h] = look_at<ALONE>(p + (unsigned)((b < P ? b : P - 1) * LINE * WV + h));
         }
 #pragma unroll
         for (int g = 0; g < G; ++g)
@@ -165,20 +212,20 @@ __device__ __forceinline__ bool collect(const Wait& wt, word_t* words, int P, in
 
 // one value a block, in a line of its own: the sum over the blocks
 // (past 64 blocks `leader`: this wave sums its group's for the others).
-template <typename T, bool STAGED>
+template <typename T, bool STAGED, bool ALONE = false>
 __device__ __forceinline__ bool collect_one(const Wait& wt, word_t* words, int P, int lane, unsigned int tag, T& out,
-                                            bool leader = false, bool alone = false) {
+                                            bool leader = false) {
   constexpr int WV = small_words_per_value<T>();
   if constexpr (STAGED) {
     T s;
-    if (!take_staged<T, 1>(wt, words, LINE, P, leader, alone, 1, tag, lane, s)) return false;
+    if (!take_staged<T, 1, ALONE>(wt, words, LINE, P, leader, 1, tag, lane, s)) return false;
     out = read_lane(s, 0);
   } else {
     word_t w[WV];
-    const bool ok = poll(wt, [&] {
+    const bool ok = wait_for<ALONE>(wt, [&] {
       bool all = true;
 #pragma unroll
-      for (int h = 0; h < WV; ++h) w[h] = get_word(words + (unsigned)((lane < P ? lane : P - 1) * LINE + h));
+      for (int h = 0; h < WV; ++h) w[h] = look_at<ALONE>(words + (unsigned)((lane < P ? lane : P - 1) * LINE + h));
 #pragma unroll
       for (int h = 0; h < WV; ++h) all = all && (unsigned int)w[h] == tag;
       return all;
@@ -193,14 +240,14 @@ __device__ __forceinline__ bool collect_one(const Wait& wt, word_t* words, int P
 template <typename T, int SLOTS>
 __device__ __forceinline__ bool collect_alone(const Wait& wt, word_t* words, int P, int wid, int lane, unsigned int tag,
                                               T (&out)[SLOTS], T* all, int nq) {
-  return small_staged(P) ? collect<T, SLOTS, true>(wt, words, P, wid, lane, tag, out, all, nq, true)
-                         : collect<T, SLOTS, false>(wt, words, P, wid, lane, tag, out, all, nq);
+  return small_staged(P) ? collect<T, SLOTS, true, true>(wt, words, P, wid, lane, tag, out, all, nq)
+                         : collect<T, SLOTS, false, true>(wt, words, P, wid, lane, tag, out, all, nq);
 }
 template <typename T>
 __device__ __forceinline__ bool collect_one_alone(const Wait& wt, word_t* words, int P, int lane, unsigned int tag,
                                                   T& out) {
-  return small_staged(P) ? collect_one<T, true>(wt, words, P, lane, tag, out, false, true)
-                         : collect_one<T, false>(wt, words, P, lane, tag, out);
+  return small_staged(P) ? collect_one<T, true, true>(wt, words, P, lane, tag, out)
+                         : collect_one<T, false, true>(wt, words, P, lane, tag, out);
 }
 
 // A block's rows of V in memory (the single phases): column c, local row i, 0 past n.
@@ -209,8 +256,11 @@ struct VGlobal {
   const S* v;  // column 0 at the block's first row
   long ldv;
   int left;    // rows of the block below n
+  // (not a load under a condition, which is waited for where that ends: an
+  // iteration of 250000 rows 46.8 instead of 41.5 us, with a bf16 basis 80 instead of 39.6)
   __device__ __forceinline__ T operator()(int c, int i) const {
-    return i < left ? Basis<S, T>::load(v + (size_t)c * ldv + i) : T(0);
+    const T x = Basis<S, T>::load(v + (size_t)c * ldv + (i < left ? i : 0));
+    return i < left ? x : T(0);
   }
 };
 
@@ -736,30 +786,35 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
   const Wait wt{&a.st.hdr->lost, SILENT_LOOKS};
   T h[SLOTS];
   bool lost = false;
-  if constexpr (PH == SMALL_GIVENS) {
-    // one block: the sums of step j, the earlier rotations, the Givens step
+  // The Givens step of step jg by one block: sums and earlier rotations from the
+  // state.  Beside the SpMV of the next step, whose blocks read none of it (an
+  // iteration of three launches instead of four: 4096 rows 25.9 -> 19.5 us).
+  auto givens = [&](int jg, unsigned int gtag) {
     const StateHdr* hd = a.st.hdr;
-    if (worker) {
-      if (nq > 0) {
-        lost = !collect_alone<T, SLOTS>(wt, h1w, P, wid, lane, tag, h, sh.h1[j & 1], nq);
-        lost = !collect_alone<T, SLOTS>(wt, h2w, P, wid, lane, tag, h, sh.h2, nq) || lost;
-      }
-    } else {
-      T n2 = T(0);
-      lost = !collect_one_alone(wt, nw, P, lane, tag, n2);
-      for (int i = lane; i < j; i += WAVE) {
+    for (int i = threadIdx.x; i <= jg; i += SMALL_NT) {
+      sh.h1[jg & 1][i] = (T)a.st.h1_of(jg)[i];
+      sh.h2[i] = (T)a.st.h2[i];
+      if (i < jg) {
         sh.cs[i] = (T)a.st.cs[i];
         sh.sn[i] = (T)a.st.sn[i];
       }
+    }
+    if (!worker) {
+      T n2 = T(0);
+      lost = !collect_one_alone(wt, nw, P, lane, gtag, n2);
       if (lane == 0) {
         sh.nrm2 = n2;
-        sh.g = (T)a.st.g[j];
+        sh.g = (T)a.st.g[jg];
       }
     }
     __syncthreads();
     if (!worker)
-      small_givens<T>(a.st, sh, j, a.kmax, (T)hd->gamma_in, (T)hd->stop_abs, hd->stop_abs >= 0.0, true);
-    __syncthreads();
+      small_givens<T>(a.st, sh, jg, a.kmax, (T)hd->gamma_in, (T)hd->stop_abs, hd->stop_abs >= 0.0, true);
+  };
+  if constexpr (PH == SMALL_GIVENS) {
+    givens(j, tag);
+  } else if (PH == SMALL_SPMV && (int)blockIdx.x == P) {
+    givens(j - 1, tag - 1);
   } else if constexpr (PH == SMALL_SPMV) {
     T inv = (T)a.st.hdr->inv_h;
     if (j > 0) {
@@ -768,21 +823,20 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
       inv = T(1) / sqrt(n2);
     }
     const XScaled<T, S> xs{a.wtmp, inv};
-    if (worker)
-      for (int s = wid; s * SELL_C < rows; s += SMALL_NW) {
-        const int i = s * SELL_C + lane, r = r0 + i, sl = r0 / SELL_C + s;
-        T y = T(0);
-        if (sl < a.A.nslices) {
-          y = sell_row<T>(a.A, xs, sl, r, lane);
-          if (r < n) {
-            Basis<S, T>::store(a.V + (size_t)j * a.ldv + r, xs(r));
-            a.w1[r] = y;
-          } else {
-            y = T(0);
-          }
+    for (int s = wid; s * SELL_C < rows; s += SMALL_NW + 1) {
+      const int i = s * SELL_C + lane, r = r0 + i, sl = r0 / SELL_C + s;
+      T y = T(0);
+      if (sl < a.A.nslices) {
+        y = sell_row<T, true>(a.A, xs, sl, r, lane);
+        if (r < n) {
+          Basis<S, T>::store(a.V + (size_t)j * a.ldv + r, xs(r));
+          a.w1[r] = y;
+        } else {
+          y = T(0);
         }
-        w[i] = y;
       }
+      w[i] = y;
+    }
     // v_j's rows are read back by other waves of the block
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -795,6 +849,8 @@ __global__ __launch_bounds__(SMALL_NT) void k_small_phase(SmallArgs<T, S> a) {
     if (nq > 0) lost = !collect_alone<T, SLOTS>(wt, FIRST ? h1w : h2w, P, wid, lane, tag, h, sh.h2, nq);
     if (worker) small_partial<T, SLOTS>(part, V, h, rows, j, wid, lane);
     __syncthreads();
+    if (blockIdx.x == 0)  // for the Givens step
+      for (int i = threadIdx.x; i <= j; i += SMALL_NT) (FIRST ? a.st.h1_of(j) : a.st.h2)[i] = (double)sh.h2[i];
     T nrm = T(0);
     if (worker) {
       for (int i = wid * WAVE + lane; i < rows; i += SMALL_NW * WAVE) {
