@@ -1093,7 +1093,8 @@ struct Ctx {
     return true;
   }
 
-  bool small_pre = false;  // with a preconditioner in the cycle kernel
+  bool small_asks = false;  // whether a block's window fits decides
+  bool small_pre = false;   // with a preconditioner in the cycle kernel
   int small_far = 0;       // distance of blocks that exchange rows
 
   // called once the solve's options are known, before its first cycle.  A
@@ -1129,7 +1130,7 @@ struct Ctx {
         return;
       }
       small_pre = true;
-      small_near(Ain, (int)sizeof(T), small_R, small_P, &st.hdr->wide, stream);  // read with the first residual
+      small_near(Ain, (int)sizeof(T), small_R, small_P, true, &st.hdr->wide, stream);  // read with the first residual
       if (poly_on) {
         std::vector<SmallStep> steps;
         for (const PStep& p : prog)
@@ -1137,6 +1138,16 @@ struct Ctx {
         (void)hipMemcpyAsync((char*)part + SMALL_PROG_AT, steps.data(), steps.size() * sizeof(SmallStep),
                              hipMemcpyHostToDevice, stream);
       }
+    }
+    // Rows that reach more of x than a block's window holds are gathered one by
+    // one, in rounds of five entries: a lane's rows times their entries is what
+    // that costs.  Scattered entries, us an iteration, general kernels and this
+    // one: fp32 100 a row, 130000 rows (8 a lane) 71, 70; 69 a row, 190000 (12)
+    // 63, 60; 45 a row, 260000 (16) 58, 57, 52 a row 61, 65; fp64 100000 rows (8),
+    // 52 a row 56, 51, 69 a row 59, 63.
+    if (!pre && small_R >= 8 * WAVE && (double)small_R / WAVE * A->nnz > (sizeof(T) == 8 ? 480.0 : 700.0) * n) {
+      small_asks = true;
+      small_near(Ain, (int)sizeof(T), small_R, small_P, false, &st.hdr->wide, stream);  // read with the first residual
     }
     small_clear(words(), small_words(small_P, (int)sizeof(T)), stream);
     // the vector as words lies in w1 and w2 (adjacent; used by the phases only)
@@ -1389,6 +1400,7 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
     c.small_far = H.wide;
     if (H.wide > SMALL_MAX_NEAR) c.small_R = 0;
   }
+  if (c.small_asks && H.wide >= SMALL_MAX_P) c.small_R = 0;
   const double beta = H.beta;
   double gamma = H.gamma;
   int status = GMRESIR_OK;
@@ -1530,6 +1542,7 @@ int arnoldi32(const gmresir_matrix* A, const double* src, int steps, char* ws, c
   Ctx<float, float> c(A, ws, L, stream, &prof);
   c.init(0.0, 0, 1.0);
   c.small_init(together, false);
+  if (c.small_asks) c.small_R = 0;  // its answer comes with a residual
   c.cast(src);
   c.cycle(steps);
   // the Hessenberg matrix and the history are copied on the stream before

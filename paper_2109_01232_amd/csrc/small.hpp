@@ -101,8 +101,9 @@ using SmallKernel = void (*)(SmallArgs<T, S>);
 template <typename T, typename S>
 SmallKernel<T, S> small_kernel(SmallPhase ph, int m, int rows, int blocks);
 
-// far: at least the distance of blocks that exchange rows, SMALL_MAX_P if a window does not fit
-void small_near(const Csr& A, int sT, int rows, int blocks, int* far, hipStream_t s);
+// far: at least the distance of blocks that exchange rows, SMALL_MAX_P if a
+// window does not fit (of the cycle kernel with a preconditioner, or without)
+void small_near(const Csr& A, int sT, int rows, int blocks, bool pre, int* far, hipStream_t s);
 
 // words of the partial sums
 size_t small_words(int blocks, int sT);

@@ -18,7 +18,7 @@ constexpr int WIN_BITS = 8192;  // chunks between the first and the last
 template <int CHUNKS_, int PAIRS_, int SLICES_>
 struct WindowMap {
   static constexpr int CHUNKS = CHUNKS_, PAIRS = PAIRS_, SLICES = SLICES_;
-  int off[PAIRS];
+  int off[PAIRS];  // more pairs: in a larger place of the caller's
   int chunk[CHUNKS];
   unsigned int bits[WIN_BITS / 32];
   int before[WIN_BITS / 32];  // set bits of the words before
@@ -26,18 +26,21 @@ struct WindowMap {
   int first;                  // chunk of bit 0
   int chunks;                 // 0: the block does not fit, the rows are gathered one by one
   int own;                    // place of the block's own first chunk
+  __device__ __forceinline__ bool wide() const { return pair[SLICES] > PAIRS; }
 };
 
 // Built once per cycle by the whole block of NT threads (all call it) for
 // slices s0 .. s0 + ns - 1, in at most `most` chunks; layout with shared offsets.
+// more: place of `room` > PAIRS pairs' entries, used where PAIRS are too few.
 template <int NT, typename W_>
-__device__ __forceinline__ void window_build(W_& W, const Csr& A, int s0, int ns, int most) {
+__device__ __forceinline__ void window_build(W_& W, const Csr& A, int s0, int ns, int most, int* more = nullptr,
+                                             int room = W_::PAIRS) {
   const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;  // a wave takes a slice, a lane an offset
   for (int i = threadIdx.x; i < WIN_BITS / 32; i += NT) W.bits[i] = 0;
   for (int s = threadIdx.x; s <= W_::SLICES; s += NT) W.pair[s] = (A.sptr[s0 + min(s, ns)] - A.sptr[s0]) / SELL_C;
   if (threadIdx.x == 0) {
     W.first = s0;
-    W.chunks = A.shared && (A.sptr[s0 + ns] - A.sptr[s0]) / SELL_C <= W_::PAIRS;
+    W.chunks = A.shared && (A.sptr[s0 + ns] - A.sptr[s0]) / SELL_C <= room;
   }
   __syncthreads();
   if (!W.chunks) return;
@@ -86,10 +89,11 @@ __device__ __forceinline__ void window_build(W_& W, const Csr& A, int s0, int ns
   };
   for (int i = threadIdx.x; i < WIN_BITS / 32; i += NT)
     for (unsigned int m = W.bits[i], k = 0; m; m &= m - 1, ++k) W.chunk[W.before[i] + k] = W.first + 32 * i + __ffs(m) - 1;
+  int* const off = W.wide() ? more : W.off;
   for (int s = wid; s < ns; s += NT / WAVE)
     for (int p = W.pair[s] + lane; p < W.pair[s + 1]; p += WAVE) {
       const int o = offset(s, p);
-      W.off[p] = place(s0 + s + (o >> 6)) * SELL_C + (o & 63);
+      off[p] = place(s0 + s + (o >> 6)) * SELL_C + (o & 63);
     }
   if (threadIdx.x == 0) W.own = place(s0);
   __syncthreads();
@@ -98,7 +102,7 @@ __device__ __forceinline__ void window_build(W_& W, const Csr& A, int s0, int ns
 // Row sums of slice s from the window, in the order of sell_row; vals: the
 // slice's values (LDS or memory), 64 per entry; U entries' loads go out together.
 template <typename T, int U = 9, typename W_>
-__device__ __forceinline__ T window_row(const W_& W, const T* x, const T* vals, int s, int lane) {
+__device__ __forceinline__ T window_row(const W_& W, const int* off, const T* x, const T* vals, int s, int lane) {
 #pragma clang fp contract(off)
   const int p0 = W.pair[s], K = W.pair[s + 1] - p0;
   T sum = T(0);
@@ -108,7 +112,7 @@ __device__ __forceinline__ T window_row(const W_& W, const T* x, const T* vals, 
     for (int u = 0; u < U; ++u) {
       const int k = k0 + u < K ? k0 + u : K - 1;
       vv[u] = vals[SELL_C * k + lane];
-      xv[u] = x[W.off[p0 + k] + lane];
+      xv[u] = x[off[p0 + k] + lane];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -117,6 +121,10 @@ __device__ __forceinline__ T window_row(const W_& W, const T* x, const T* vals, 
     }
   }
   return sum;
+}
+template <typename T, int U = 9, typename W_>
+__device__ __forceinline__ T window_row(const W_& W, const T* x, const T* vals, int s, int lane) {
+  return window_row<T, U>(W, W.off, x, vals, s, lane);
 }
 
 }  // namespace gir
