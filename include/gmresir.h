@@ -201,7 +201,9 @@ size_t gmresir_workspace_bytes(const gmresir_matrix* A, const gmresir_params* p)
    the first columns of the basis in registers, for larger systems without a
    preconditioner up to 2^21 rows (2^20 in fp64 or with ortho 1, 2^19 at fewer
    than 6 nonzeros a row) at restart <= 64, if the rows of x that a 256th of the
-   rows reach fit a compute unit's LDS.  Other systems of n <= 2^18 record the
+   rows reach fit a compute unit's LDS.  Neither has very short cycles (restart or
+   inner_cap below 2 to 4, for the larger systems below 4 to 38 the more rows
+   there are), which the others make faster.  Other systems of n <= 2^18 record the
    kernels of a cycle once as a HIP graph, replayed for every later cycle of the
    same length.  With profile = 1 and in gmresir_solve_noalloc every kernel is
    launched directly; the bits are the same, but for the larger systems, with a

@@ -56,10 +56,37 @@ namespace {
 constexpr int MAX_GRID = 1024;  // <= MAX_BLOCKS (partials per reduction)
 // Systems of more rows run the cycle kernel of mid.hip where it takes them (up
 // to 2^21 rows, 2^20 in fp64): from a little past the limits of the one of
-// small.hip, the smallest sizes measured.  It is the faster one over all of
-// that range: solves of 263169 rows 88.5 -> 41.8 ms, 27-point of 1030301 24.8
-// -> 18.7, of 2^21 50.3 -> 42.9; fp64 136900 rows 59.7 -> 34.7, 1030301 50.7 -> 40.0.
-int64_t mid_min_n(int m, int sT) { return (sT == 4 && m <= 56 ? 1 << 18 : 1 << 17) + 1024; }
+// small.hip, the smallest sizes measured.  Below them that one is faster (fp64
+// GMRES(20), 7-point 58^3: 22.5 us an iteration, this one 28.2, the general
+// kernels 37.8).  Whole GMRES(50) solves, general kernels and this one: 263169
+// rows 88.5, 41.8 ms, 27-point of 1030301 24.8, 18.7, of 2^21 50.3, 42.9; fp64
+// 136900 rows 59.7, 34.7, 1030301 50.7, 40.0.
+int64_t mid_min_n(int m, int sT) { return ((sT == 4 && m <= 56) || m <= 28 ? 1 << 18 : 1 << 17) + 1024; }
+
+// Steps of a cycle from which on that kernel is the faster one: it reads fewer
+// columns per step, but its SpMV gathers from one window per compute unit and
+// each cycle is a cooperative launch.  By slices of 64 rows per block (the more,
+// the fewer columns are resident) at most 20, 32, 40, 64 and more, the first
+// number of steps at which no stencil measured (5-point 2D, 7-, 19- and 27-point
+// 3D at 270400 to 2048383 rows, m = 4 to 50) was slower than with the general
+// kernels.  us an iteration of 7-point 101^3 (63 slices), general kernels and
+// this one: fp32 m = 8 51, 63, m = 25 57, 52; fp64 m = 12 69, 96, m = 30 95, 87.
+int mid_min_steps(int64_t slices, int sT, int sS, bool ls, bool wide) {
+  static const int first[][5] = {{4, 8, 14, 25, 30},     // fp32
+                                 {4, 8, 12, 27, 36},     // fp32, bf16 basis
+                                 {12, 22, 24, 26, 26},   // fp64
+                                 {5, 18, 24, 38, 38},    // fp32, one reduction in the general kernels
+                                 {20, 34, 65, 65, 65}};  // fp64, the same (65: never)
+  const int64_t s = (slices + MID_BLOCKS - 1) / MID_BLOCKS;
+  const int size = s <= 20 ? 0 : s <= 32 ? 1 : s <= 40 ? 2 : s <= 64 ? 3 : 4;
+  const int kind = ls ? (sT == 8 ? 4 : 3) : sT == 8 ? 2 : sS == 2 ? 1 : 0;
+  return kind == 4 && size > 1 && wide ? 45 : first[kind][size];
+}
+
+// The same of the kernel of small.hip.  A cycle's cooperative launch takes 10 us
+// more than a replayed graph (5-point 64^2, cycles of one step 67, 76 us, of two
+// 42, 40; 500^2, of two 49, 52, of three 43, 40; fp64 one reduction 42, 43).
+int small_min_steps(int64_t n) { return n <= 1 << 15 ? 2 : 4; }
 constexpr int64_t GRAPH_MAX_N = 1 << 18;  // cycles of smaller systems run as HIP graphs
 constexpr size_t ALIGN = 256;
 
@@ -1042,6 +1069,7 @@ struct Ctx {
   // larger systems: the cycle as one cooperative launch with part of the basis
   // in registers (mid.hip); nullptr: not this path
   MidKernel<T, S> mid_k{};
+  int cycle_steps = INT_MAX;  // of a full cycle
 
   void mid_init() {
     if (!A->sell_shared || L.bj > 0 || poly_on || prof->on || L.m > MID_MAX_M ||
@@ -1056,6 +1084,7 @@ struct Ctx {
     // ortho 1 reads the basis twice an iteration: faster than three times in
     // part past 2^20 rows (1157625: 23.1, 24.2 ms; 512000: 13.1, 10.2)
     if (L.ls && n > 1 << 20) return;
+    if (cycle_steps < mid_min_steps(A->nslices, (int)sizeof(T), (int)sizeof(S), L.ls, A->sell_wide)) return;
     mid_k = mid_kernel<T, S>(A->nslices, A->sell_wide);
     if (!mid_k.k) return;
     small_clear(words(), mid_words(), stream);
@@ -1108,7 +1137,7 @@ struct Ctx {
     // and the LDS has room for the polynomial's vectors; every size that
     // qualifies is faster (900 rows 4.0 -> 1.0 ms a solve, 216000 18.7 -> 16.4)
     const bool pre = L.bj > 0 || poly_on;
-    if (mid_k.k || !A->sell_shared) return;
+    if (mid_k.k || !A->sell_shared || cycle_steps < small_min_steps(n)) return;
     small_R = small_rows(n, L.m, (int)sizeof(T), device_cus(A->device));
     if (small_R == 0) return;
     small_P = (n + small_R - 1) / small_R;
@@ -1387,6 +1416,7 @@ int solve_impl(const gmresir_matrix* A, const double* b, double* x, const gmresi
     set_error("internal: block-Jacobi buffers missing from the workspace layout");
     return GMRESIR_ERR_INVALID_ARG;
   }
+  c.cycle_steps = std::min(m, cap);
   c.init(p->rtol, p->check_mode, 0.0);
   c.small_init(allow_graph, allow_graph);
   if (L.bj > 0) c.bj_setup();
