@@ -1652,10 +1652,15 @@ namespace {
 
 // The row tiles of a matrix with rows longer than TILE_MAX_ROW, cut greedily
 // on the host: <= TILE_ROWS rows and <= TILE_NNZ nonzeros, or one longer row.
-int cut_tiles(int64_t n, const int32_t* rowptr, int32_t* tile_row, hipStream_t s, int32_t* ntiles, int32_t* lds_nnz) {
-  std::vector<int32_t> rp(n + 1), tiles;
-  HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+// rp: the row pointers, or empty if they are still to be copied.
+int cut_tiles(int64_t n, const int32_t* rowptr, std::vector<int32_t>& rp, int32_t* tile_row, hipStream_t s,
+              int32_t* ntiles, int32_t* lds_nnz) {
+  std::vector<int32_t> tiles;
+  if (rp.empty()) {
+    rp.resize(n + 1);
+    HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  }
   tiles.push_back(0);
   int64_t r0 = 0;
   while (r0 < n) {
@@ -1799,13 +1804,21 @@ int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const i
   S.sv32 = (float*)((char*)S.scol + align_up(E * 4));
   S.sv64 = (double*)((char*)S.sv32 + align_up(E * 4));
   const size_t seg_lds = (size_t)(TILE_SEG + TILE_SPAN + 1) * sizeof(int);
-  const size_t scan_lds = std::max(seg_lds, (size_t)NWAVES * S.cap * sizeof(int));
+  const size_t scan_lds = std::max(seg_lds, (size_t)NWAVES * (S.cap + UNION_SLOTS) * sizeof(int));
   const size_t build_lds = std::max(seg_lds, (size_t)NWAVES * S.cap * (sizeof(int) + sizeof(double)));
   hipLaunchKernelGGL(k_setup_scan, dim3(S.nblocks + (S.nseg > 1 ? S.nseg : 0)), dim3(BLOCK), scan_lds, s, S);
   hipLaunchKernelGGL(k_setup_decide, dim3(1), dim3(SETUP_MAX_BLOCKS), 0, s, S);
-  hipLaunchKernelGGL(k_setup_build, dim3(S.nblocks + S.nseg), dim3(BLOCK), build_lds, s, S);
+  // a matrix without slices has its values' fp32 copy made by four loads a thread
+  const int extra = std::max<int>(0, (int)std::min<int64_t>(SETUP_MAX_BLOCKS, nnz / (4 * BLOCK)) - S.nblocks);
+  hipLaunchKernelGGL(k_setup_build, dim3(S.nblocks + S.nseg + extra), dim3(BLOCK), build_lds, s, S);
   HIP_TRY(hipGetLastError());
   SetupDecision dec;
+  // rows this long are cut into tiles on the host: their pointers come along
+  std::vector<int32_t> rp;
+  if (nnz > n * (TILE_MAX_ROW / 2)) {
+    rp.resize(n + 1);
+    HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  }
   HIP_TRY(hipMemcpyAsync(&dec, S.dec, sizeof(dec), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (dec.first != 0 || dec.last != nnz) {
@@ -1818,7 +1831,7 @@ int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const i
   }
   if (dec.max_len > TILE_MAX_ROW) {
     // a row so long that tiles need not start on multiples of 8 rows
-    if (int e = cut_tiles(n, rowptr, S.tile_row, s, &dec.ntiles, &dec.lds_nnz)) return e;
+    if (int e = cut_tiles(n, rowptr, rp, S.tile_row, s, &dec.ntiles, &dec.lds_nnz)) return e;
   }
   gmresir_matrix* A = new gmresir_matrix;
   A->sell = dec.sell != 0;

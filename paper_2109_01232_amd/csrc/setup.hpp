@@ -12,8 +12,9 @@
 //
 // Bound by memory: the CSR arrays are read once (the column indices twice) and
 // every copy is written once.  7-point 150^3 (23.5 M nonzeros), set-up and
-// one product in each precision: 0.40 ms (scan 80 us, decide 29, build 184), where copying the row pointers and
-// column indices to the host and walking them there took 38.0 ms.
+// one product in each precision: 0.39 ms (scan 70 us, decide 30, build 190),
+// where copying the row pointers and column indices to the host and walking them
+// there took 38.0 ms.
 #pragma once
 
 #include "device.hpp"
@@ -21,7 +22,7 @@
 namespace gir {
 
 constexpr int SETUP_MAX_BLOCKS = 1024;  // = threads of k_setup_decide
-constexpr int SETUP_MIN_SLICES = 16;    // slices per block at least
+constexpr int SETUP_MIN_SLICES = NWAVES;  // slices per block at least: one a wave
 constexpr int SETUP_CHUNK = 256;        // slices whose pointers a block scans at once
 // Tiles start on multiples of 8 rows ("units") as long as 8 rows fit a tile,
 // i.e. no row is longer than TILE_NNZ / 8; longer rows go through the host.
@@ -29,6 +30,11 @@ constexpr int TILE_UNIT = 8;
 constexpr int TILE_SPAN = TILE_ROWS / TILE_UNIT;  // units of a tile at most
 constexpr int TILE_SEG = 1024;                    // units per segment of the tile chain
 constexpr int TILE_MAX_ROW = TILE_NNZ / TILE_UNIT;
+
+// Offsets of a slice's rows seen so far, a hash table in LDS: SELL_MAX_ROW and a
+// step's 64 more are the most it holds.
+constexpr int UNION_SLOTS = 1024;
+static_assert(SELL_MAX_ROW + WAVE < UNION_SLOTS, "the table never fills");
 
 enum : int32_t { SETUP_LONG = 1, SETUP_UNORDERED = 2, SETUP_FAR = 4 };
 
@@ -54,7 +60,8 @@ static_assert(sizeof(SetupDecision) == 64, "SetupDecision");
 
 // What the set-up kernels read and write.  The scratch (decision, infos, tile
 // chain tables) lies in the tile table's region behind its largest possible
-// number of tiles, n / 8 + 2 (setup_scratch_bytes of the n + 1 entries).
+// number of tiles, n / 8 + 2 (of the max_tiles + 1 = n + 1 that
+// the region has room for).
 struct Setup {
   int n;
   long long nnz;
@@ -121,6 +128,19 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Adds the offset d of each lane that has one; the number that were new.
+__device__ __forceinline__ int union_add(int* table, int d, bool has) {
+  bool added = false;
+  for (unsigned at = (unsigned)d * 2654435761u >> 22; __any(has); at = (at + 1) % UNION_SLOTS) {
+    if (!has) continue;
+    int old = table[at];
+    if (old == INT32_MIN) old = atomicCAS(&table[at], INT32_MIN, d);
+    added = added || old == INT32_MIN;
+    has = old != INT32_MIN && old != d;
+  }
+  return __popcll(__ballot(added));
+}
+
 __device__ __forceinline__ int wave_max_int(int v) {
 #pragma unroll
   for (int o = WAVE / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, WAVE));
@@ -168,6 +188,7 @@ __global__ __launch_bounds__(BLOCK) void k_setup_scan(Setup S) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   int* sc = lds + wid * S.cap;
+  int* const table = lds + NWAVES * S.cap + wid * UNION_SLOTS;
   const int s0 = (int)((long long)S.ns * blockIdx.x / S.nblocks);
   const int s1 = (int)((long long)S.ns * (blockIdx.x + 1) / S.nblocks);
   long long sumK = 0, sumU = 0;
@@ -193,34 +214,74 @@ __global__ __launch_bounds__(BLOCK) void k_setup_scan(Setup S) {
       const int q0 = __builtin_amdgcn_readlane(p0, 0);
       const int cnt = __builtin_amdgcn_readlane(p1, rows - 1) - q0;
       const int a = r < S.n ? p0 - q0 : 0, b = r < S.n ? p1 - q0 : 0;
-      auto look = [&](const int* cols) {
-        bool unordered = false, far = false;
+      // Each lane walks its row beside the longest one's.  Rows that all begin
+      // as that one does (the inside of a stencil's grid) have its offsets for
+      // their union.  Others' are merged, smallest offset by smallest offset:
+      // quick where the lanes share most of them (a grid's edge), else as many
+      // steps as there are entries, so past twice the longest row's the union is
+      // counted in the table (1000 random rows of 20 entries, whole set-up, 703
+      // -> 78 us; 300000 836 -> 214).  Slices too large to stage are not
+      // merged, each step would read memory.
+      auto look = [&](const int* cols, bool staged) {
+        constexpr int AHEAD = 4;  // entries loaded together
+        const int longest = __ffsll(__ballot(len == K)) - 1;
+        bool unordered = false, far = false, differ = false;
         int prev = 0;
-        for (int p = a; p < b; ++p) {
-          const int d = cols[p] - r;
-          unordered = unordered || (p > a && d <= prev);
-          far = far || d > 32767 || d < -32767;
+        auto walk = [&](auto step) {
+          for (int k0 = 0; k0 < K; k0 += AHEAD) {
+            int d[AHEAD];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) d[u] = cols[min(a + k0 + u, cnt - 1)] - r;
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+              if (k0 + u < K) step(k0 + u, d[u], a + k0 + u < b);
+          }
+        };
+        walk([&](int k, int d, bool has) {
+          unordered = unordered || (has && k > 0 && d <= prev);
+          far = far || (has && (d > 32767 || d < -32767));
+          differ = differ || (has && d != __builtin_amdgcn_readlane(d, longest));
           prev = d;
-        }
+        });
         if (__any(far)) flags |= SETUP_FAR;
         if (__any(unordered)) {
           flags |= SETUP_UNORDERED;
-        } else {
+          return;
+        }
+        U = K;
+        if (!__any(differ)) return;
+        if (staged) {
           SliceCursor cu;
           cu.start(cols, r, a, b);
           int m, at;
           bool hit;
-          while (U <= SELL_MAX_ROW && cu.next(m, hit, at)) ++U;
-          if (U > SELL_MAX_ROW) flags |= SETUP_UNORDERED;
+          for (U = 0; U <= 2 * K; ++U)
+            if (!cu.next(m, hit, at)) break;
         }
+        if (!staged || U > 2 * K) {
+          for (int i = lane; i < UNION_SLOTS; i += WAVE) table[i] = INT32_MIN;
+          wave_lds_sync();
+          U = 0;
+          walk([&](int, int d, bool has) {
+            if (U <= SELL_MAX_ROW) U += union_add(table, d, has);
+          });
+        }
+        if (U > SELL_MAX_ROW) flags |= SETUP_UNORDERED;
       };
       if (cnt <= S.cap) {
-        for (int i = lane; i < cnt; i += WAVE) sc[i] = S.col[q0 + i];
+        for (int i = lane; i < cnt; i += 4 * WAVE) {
+          int c[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) c[u] = S.col[q0 + min(i + u * WAVE, cnt - 1)];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (i + u * WAVE < cnt) sc[i + u * WAVE] = c[u];
+        }
         wave_lds_sync();
-        look(sc);
+        look(sc, true);
         wave_lds_sync();  // sc is free for the next slice
       } else {
-        look(S.col + q0);
+        look(S.col + q0, false);
       }
     }
     const int Kc = min(K, SELL_MAX_ROW + 1);
@@ -372,11 +433,28 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
   const SetupDecision* dec = S.dec;
   if (dec->bad_row != INT32_MAX || dec->first != 0 || dec->last != S.nnz) return;
   char* lds = dyn_lds<char>();
-  if ((int)blockIdx.x >= S.nblocks) {
+  const bool sell = dec->sell, shared = dec->shared, d16 = dec->d16;
+  const int extra = (int)blockIdx.x - S.nblocks - S.nseg;  // blocks for the fp32 copy alone
+  if ((int)blockIdx.x >= S.nblocks && extra < 0) {
     if (dec->max_len <= TILE_MAX_ROW) tile_emit(S, blockIdx.x - S.nblocks, (int*)lds);
     return;
   }
-  const bool sell = dec->sell, shared = dec->shared, d16 = dec->d16;
+  if (!sell) {
+    // no slices to fill: the values alone, over as many blocks as they need
+    // (slice by slice, 3000 rows of 550 entries, 750 us)
+    const long long stride = (long long)(gridDim.x - S.nseg) * BLOCK;
+    for (long long i = (long long)(extra < 0 ? (int)blockIdx.x : S.nblocks + extra) * BLOCK + threadIdx.x; i < S.nnz;
+         i += 4 * stride) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = S.vals[i + u * stride < S.nnz ? i + u * stride : i];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + u * stride < S.nnz) S.v32[i + u * stride] = (float)v[u];
+    }
+    return;
+  }
+  if (extra >= 0) return;
   __shared__ int s_base[SETUP_CHUNK], s_wave[NWAVES];
   const int lane = threadIdx.x & (WAVE - 1);
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -387,30 +465,28 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
   int before = (int)(shared ? S.info[blockIdx.x].sumU : S.info[blockIdx.x].sumK);  // slots / 64 of the slices before
   for (int c0 = s0; c0 < s1; c0 += SETUP_CHUNK) {
     const int c1 = min(c0 + SETUP_CHUNK, s1);
-    if (sell) {
-      // slice pointers of the chunk: exclusive sums of the slices' widths
-      const int s = c0 + (int)threadIdx.x;
-      const int w = s < c1 ? S.sptr[s] : 0;
-      const int width = shared ? w & 0xffff : w >> 16;
-      int x = width;
+    // slice pointers of the chunk: exclusive sums of the slices' widths
+    const int mine = c0 + (int)threadIdx.x;
+    const int w = mine < c1 ? S.sptr[mine] : 0;
+    const int width = shared ? w & 0xffff : w >> 16;
+    int x = width;
 #pragma unroll
-      for (int o = 1; o < WAVE; o *= 2) {
-        const int y = __shfl_up(x, o, WAVE);
-        if (lane >= o) x += y;
-      }
-      if (lane == WAVE - 1) s_wave[wid] = x;
-      __syncthreads();
-      int at = before, sum = 0;
-      for (int q = 0; q < NWAVES; ++q) {
-        if (q < wid) at += s_wave[q];
-        sum += s_wave[q];
-      }
-      s_base[threadIdx.x] = at + x - width;
-      if (s < c1) S.sptr[s] = SELL_C * (at + x - width);
-      before += sum;
-      __syncthreads();
-      if (c1 == S.ns && threadIdx.x == 0) S.sptr[S.ns] = SELL_C * before;
+    for (int o = 1; o < WAVE; o *= 2) {
+      const int y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
     }
+    if (lane == WAVE - 1) s_wave[wid] = x;
+    __syncthreads();
+    int at = before, sum = 0;
+    for (int q = 0; q < NWAVES; ++q) {
+      if (q < wid) at += s_wave[q];
+      sum += s_wave[q];
+    }
+    s_base[threadIdx.x] = at + x - width;
+    if (mine < c1) S.sptr[mine] = SELL_C * (at + x - width);
+    before += sum;
+    __syncthreads();
+    if (c1 == S.ns && threadIdx.x == 0) S.sptr[S.ns] = SELL_C * before;
     for (int s = c0 + wid; s < c1; s += NWAVES) {
       const int r = s * SELL_C + lane;
       const int rows = min(SELL_C, S.n - s * SELL_C);
@@ -426,7 +502,6 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
           sc[i] = S.col[q0 + i];
         }
       }
-      if (!sell) continue;
       const int a = r < S.n ? p0 - q0 : 0, b = r < S.n ? p1 - q0 : 0;
       const int base = s_base[s - c0];
       const int K = (s + 1 < c1 ? s_base[s + 1 - c0] : before) - base;

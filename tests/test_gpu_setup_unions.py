@@ -1,0 +1,104 @@
+"""Matrix set-up where the rows of a slice differ: sizes of the union of their
+offsets (a table in LDS), and the time of the set-up.
+
+Tables against the plain restatement of the set-up's rules.  Cases: rows that
+part at the first step, after a few and after more than a wave's width of them;
+rows that end early; unions of 511 to 513 offsets, the most a slice's list may
+have, of equal and of scattered offsets; offsets that collide in the table;
+slices staged in LDS and read from memory.  Times against the set-up of a band
+of the same size, which needs no table."""
+import ctypes
+import time
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2109_01232_amd import binding as B
+from paper_2109_01232_amd import problems as P
+
+from gpu_common import say
+from test_gpu_setup import check, random_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.lib()
+
+
+def rows_of(n, offsets_of):
+    """Row r has the columns r + o in range, o from offsets_of(r)."""
+    cols = [np.array(sorted(r + o for o in offsets_of(r) if 0 <= r + o < n)) for r in range(n)]
+    rowptr = np.concatenate([[0], np.cumsum([len(c) for c in cols])])
+    rng = np.random.default_rng(n)
+    return P.CSR(n, rowptr.astype(np.int32), np.concatenate(cols).astype(np.int32), rng.standard_normal(rowptr[-1]))
+
+
+def union_of(count, base=440, step=1):
+    """Rows of `base` offsets whose slices' union has `count`: each row starts at another one."""
+    return lambda r: [step * ((r % 64) * (count - base) // 63 + k) for k in range(base)]
+
+
+CASES = {
+    "first_step": lambda: rows_of(1000, lambda r: (-3 + r % 2, 1, 2)),
+    "later_step": lambda: rows_of(3000, lambda r: [*range(-2, 3), 7 + r % 5]),
+    "after_a_wave": lambda: rows_of(3000, lambda r: [*range(-40, 41), 50 + r % 3, 60]),
+    "short_rows": lambda: rows_of(3000, lambda r: list(range(r % 64 + 1))),
+    "short_rows_differ": lambda: rows_of(3000, lambda r: [*range(min(r % 64, 20)), 30 + r % 7]),
+    "union_511": lambda: rows_of(4096, union_of(511)), "union_512": lambda: rows_of(4096, union_of(512)),
+    "union_513": lambda: rows_of(4096, union_of(513)),
+    "union_512_strided": lambda: rows_of(4096, union_of(512, step=3)),
+    "colliding": lambda: rows_of(70000, lambda r: (-1024 * (r % 3), 0, 1024 * (1 + r % 4), 2048 * 16)),
+    "random_20": lambda: random_rows(1000, np.full(1000, 20), 1),
+    "random_200": lambda: random_rows(3000, np.full(3000, 200), 2),
+    "near_100": lambda: random_rows(2000, np.full(2000, 100), 3, span=150),
+    "random_330": lambda: random_rows(2000, np.full(2000, 330), 4),
+    "random_600": lambda: random_rows(1500, np.full(1500, 600), 5),
+}
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_tables(case):
+    say("setup unions", case)
+    layout = check(CASES[case]())
+    assert layout == {"union_511": 3, "union_512": 3, "union_512_strided": 3, "union_513": 2, "after_a_wave": 3,
+                      "random_600": 0}.get(case, layout)
+
+
+def create_us(A):
+    rp, ci, v = (torch.from_numpy(np.ascontiguousarray(t)).cuda() for t in (A.rowptr, A.colidx, A.vals))
+    need = B.lib().gmresir_matrix_storage_bytes(A.n, A.nnz)
+    store = torch.empty(need, dtype=torch.uint8, device="cuda")
+    best = 1e9
+    for _ in range(12):
+        h = ctypes.c_void_p()
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        st = B.lib().gmresir_matrix_create(A.n, A.nnz, rp.data_ptr(), ci.data_ptr(), v.data_ptr(), store.data_ptr(),
+                                           need, torch.cuda.current_stream().cuda_stream, ctypes.byref(h))
+        best = min(best, 1e6 * (time.perf_counter() - t))
+        assert st == 0
+        B.lib().gmresir_matrix_destroy(h)
+    return best
+
+
+@pytest.mark.parametrize("n,k,times", [(1000, 20, 3.0), (3000, 20, 3.0), (30000, 20, 5.0), (2000, 600, 5.0)])
+def test_time(n, k, times):
+    """Taking the union offset by offset and copying the values slice by slice
+    these were at 12, 12, 14 and 19 times the band's set-up."""
+    say("setup time", n, k)
+    rng = np.random.default_rng(0)
+    cols = np.sort(rng.integers(0, n, (n, k)), 1)
+    keep = np.diff(cols, axis=1, prepend=-1) > 0
+    rowptr = np.concatenate([[0], np.cumsum(keep.sum(1))])
+    A = P.CSR(n, rowptr.astype(np.int32), cols[keep].astype(np.int32), rng.standard_normal(rowptr[-1]))
+    w = min(k, 20) // 2
+    band = rows_of(min(n, 3000), lambda r: range(-w, w + 1))
+    t, tb = create_us(A), create_us(band)
+    print(f"{t:.0f} and {tb:.0f} us")
+    assert t <= times * tb
