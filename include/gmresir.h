@@ -15,10 +15,10 @@
  *  - Pointers are HIP device pointers owned by the caller unless the
  *    parameter name ends in _host.  The library never calls hipMalloc or
  *    hipFree: every device buffer holding data is passed in.  (Host-side
- *    handles are allocated with malloc/new; gmresir_solve on systems of at
- *    most 2^18 rows launches its inner cycle cooperatively or records it as a
- *    HIP graph, and profiling creates HIP events -- runtime objects the HIP
- *    runtime backs itself.)
+ *    handles are allocated with malloc/new; gmresir_solve launches the inner
+ *    cycle of systems of up to 2^21 rows cooperatively or, up to 2^18 rows,
+ *    records it as a HIP graph, and profiling creates HIP events -- runtime
+ *    objects the HIP runtime backs itself.)
  *  - Work is enqueued on the caller's `stream` (a hipStream_t passed as
  *    void*; NULL is the legacy default stream).  Functions that return host
  *    values synchronise that stream before returning.
@@ -69,7 +69,8 @@ enum gmresir_category {
   GMRESIR_CAT_POLY = 3,        /* SpMV steps of p(A) */
   GMRESIR_CAT_REFINE = 4,      /* correction x += gamma V y, r = b - A x (fp64), cast of r */
   GMRESIR_CAT_OTHER = 5,       /* fallbacks for restart lengths beyond the fused limit */
-  GMRESIR_CAT_TAIL = 6,        /* one-block tails: sums of h1, h2, ||w||^2; Hessenberg column, Givens update */
+  GMRESIR_CAT_TAIL = 6,        /* one-block tails: sums of h1, h2, ||w||^2; Hessenberg column, Givens update
+                                  (small systems launched kernel by kernel: beside the next SpMV) */
   GMRESIR_NCAT = 7
 };
 
@@ -123,7 +124,8 @@ typedef struct {
   double solve_s;            /* host wall time of the call */
   double cat_time_s[GMRESIR_NCAT];  /* device time per category (profile = 1) */
   double cat_bytes[GMRESIR_NCAT];   /* algorithmic HBM bytes per category (always filled) */
-  int64_t cat_launches[GMRESIR_NCAT];
+  int64_t cat_launches[GMRESIR_NCAT]; /* kernels per category (always filled); a cycle made by one kernel
+                                         counts as the separate kernels whose work it does */
 } gmresir_result;
 
 /* ---- matrix ------------------------------------------------------------ */

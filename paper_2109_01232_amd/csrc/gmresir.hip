@@ -1056,7 +1056,7 @@ struct Ctx {
   }
 
   // -------------------------------------------------------------------------
-  // systems whose basis fits the compute units' LDS: the cycle as one
+  // systems whose basis fits the compute units' registers: the cycle as one
   // cooperative launch, or its phases one by one (small.hpp)
   // -------------------------------------------------------------------------
 
@@ -1079,7 +1079,11 @@ struct Ctx {
     // are off by 0.5-3e-9, and where another order of sums ends the refinement
     // a step earlier or later they move by as much (1.8e-9 for one of five
     // right-hand sides at 10^6 rows): those keep the general kernels' order
-    // (211 ms a solve instead of 149).  Wider rows move by 3e-11 at most.
+    // (211 ms a solve instead of 149).  Measured with them: 7-point anisotropic
+    // convection-diffusion of 531441 to 2048383 rows, five right-hand sides each,
+    // moves by 6e-12 at most where its error is 0.7-3e-10.  Neither the rows nor
+    // their width measure the conditioning that decides: a better conditioned
+    // five-point system gives up 1.4 times for nothing.
     if (n > 1 << 19 && A->nnz < 6 * n) return;
     // ortho 1 reads the basis twice an iteration: faster than three times in
     // part past 2^20 rows (1157625: 23.1, 24.2 ms; 512000: 13.1, 10.2)
@@ -1124,7 +1128,8 @@ struct Ctx {
 
   bool small_asks = false;  // whether a block's window fits decides
   bool small_pre = false;   // with a preconditioner in the cycle kernel
-  int small_far = 0;       // distance of blocks that exchange rows
+  int small_far = 0;        // distance of blocks that exchange rows
+  std::vector<SmallStep> small_prog;  // the preconditioner's program, until it has been copied
 
   // called once the solve's options are known, before its first cycle.  A
   // cycle in one kernel makes two-pass CGS2 with ortho 1 too: what the delayed
@@ -1161,11 +1166,13 @@ struct Ctx {
       small_pre = true;
       small_near(Ain, (int)sizeof(T), small_R, small_P, true, &st.hdr->wide, stream);  // read with the first residual
       if (poly_on) {
-        std::vector<SmallStep> steps;
         for (const PStep& p : prog)
-          steps.push_back({{p.ay, p.aw, p.ax, p.at, p.bw, p.bx, p.bt}, p.w, p.d, p.has_y, p.y_read});
-        (void)hipMemcpyAsync((char*)part + SMALL_PROG_AT, steps.data(), steps.size() * sizeof(SmallStep),
-                             hipMemcpyHostToDevice, stream);
+          small_prog.push_back({{p.ay, p.aw, p.ax, p.at, p.bw, p.bx, p.bt}, p.w, p.d, p.has_y, p.y_read});
+        if (hipMemcpyAsync((char*)part + SMALL_PROG_AT, small_prog.data(), small_prog.size() * sizeof(SmallStep),
+                           hipMemcpyHostToDevice, stream) != hipSuccess) {
+          small_R = 0;  // the next call of the runtime reports it
+          return;
+        }
       }
     }
     // Rows that reach more of x than a block's window holds are gathered one by

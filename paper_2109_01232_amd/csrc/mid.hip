@@ -4,7 +4,7 @@
 // The chip's 256 compute units have 128 MB of vector registers, half of the
 // basis of GMRES(50) on 10^6 rows.  A block keeps its rows of the first
 // columns there for the whole cycle (64 MB: half of the registers) and reads
-// only the later ones from memory (1000^2, fp32: 16 resident columns, on
+// only the later ones from memory (10^6 rows in fp32: 16 resident columns, on
 // average 12 instead of 25 are read per sweep); the work vectors w, w', w''
 // and the rows of x the SpMV gathers never leave LDS.
 //
@@ -15,12 +15,14 @@
 // blocks: 1.8 us for all 256, where every block reading every other's line
 // takes 5 us.
 //
-// Bound by memory where most columns are read (the first projection of 1000^2:
-// 5.6 TB/s), by the vector units and LDS barriers where most are resident.
-// Whole solves to 1e-12, GMRES(50), against one kernel per operation: fp32
-// 5-point 513^2 88.5 -> 41.8 ms, 600^2 98.8 -> 53.2, 27-point 80^3 15.8 -> 10.3,
-// 101^3 24.8 -> 18.7, 128^3 50.3 -> 42.9; bf16 basis 80^3 17.3 -> 11.9, 128^3
-// 42.5 -> 37.2; fp64 7-point 52^3 28.6 -> 16.1, 27-point 101^3 50.7 -> 40.0.
+// Bound by memory where most columns are read (27-point 128^3 in fp32: 705 MB
+// an iteration at 4.6 TB/s), by the vector units and LDS barriers where most are
+// resident; with few columns to read the general kernels are faster (see
+// mid_min_steps).  Whole solves to 1e-12, GMRES(50), against one kernel per
+// operation: fp32 5-point 513^2 88.5 -> 41.8 ms, 600^2 98.8 -> 53.2, 27-point
+// 80^3 15.8 -> 10.3, 101^3 24.8 -> 18.7, 128^3 50.3 -> 42.9; bf16 basis 80^3 17.3
+// -> 11.9, 128^3 42.5 -> 37.2; fp64 7-point 52^3 28.6 -> 16.1, 27-point 101^3
+// 50.7 -> 40.0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

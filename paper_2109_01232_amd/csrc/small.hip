@@ -1,4 +1,4 @@
-// Kernels of the LDS-resident inner cycle (see small.hpp).
+// Kernels of the register-resident inner cycle (see small.hpp).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

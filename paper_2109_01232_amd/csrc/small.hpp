@@ -1,20 +1,20 @@
-// Inner cycles of systems whose Krylov basis fits the LDS of the GPU's
+// Inner cycles of systems whose Krylov basis fits the registers of the GPU's
 // compute units (declarations; kernels in small.hip).
 //
 // A cycle of such a system is bound by latency: as separate kernels an
 // iteration is five dependent launches of a few microseconds each whatever the
-// rows.  Here the rows are split over at most one block per compute unit, each
-// block keeps its rows of V in LDS, and one cooperative launch runs the whole
-// cycle.  The three reductions of an iteration (h1, h2, ||w''||^2) are
-// exchanges between the blocks: a block stores its partial sums as 64-bit
-// words of value and tag, and every block reads and sums all of them in the
-// same order.  A word is complete when its tag is the iteration's, so an
-// exchange is one store and one load in flight, without flags, fences or a
-// second trip.
+// rows.  Here the rows are split over at most one block per compute unit, the
+// waves of a block keep its rows of V in registers, and one cooperative launch
+// runs the whole cycle.  The three reductions of an iteration (h1, h2, ||w''||^2)
+// are exchanges between the blocks: a block stores its partial sums as 64-bit
+// words of value and tag, and every block adds all of them in the same order,
+// past 64 blocks in two stages.  A word is complete when its tag is the
+// iteration's, so an exchange is one store and one load in flight, without
+// flags, fences or a second trip.
 //
 // The same phases can be launched one by one (profiling, the allocation-free
-// entry point, or when a cooperative launch is refused): the same partition,
-// order of operations and words, so the same bits.
+// entry point, a cooperative launch that is refused or whose blocks are not all
+// on the GPU): the same partition, order of operations and words, so the same bits.
 #pragma once
 
 #include "device.hpp"

@@ -7,11 +7,12 @@ Bars, as for two-pass CGS2: fp64 cycle histories within 1e-10 of the
 oracle's (same algorithm, rounding-level differences), fp32 cycle histories
 within 1e-5, solutions within 1e-8 relative at a parity tolerance
 rtol = 1e-12, final fp64 residuals <= rtol; iteration counts equal in fp64 and
-within one restart cycle in fp32.  Systems of at least 65,536 rows take the
-fused sliced SpMV + reduction kernel; smaller ones the plain SpMV and a
-separate reduction kernel; both are covered, with ragged row counts, every
-column-count class (m = 1 .. 128), and the polynomial and block-Jacobi
-preconditioners."""
+within one restart cycle in fp32.  Systems whose cycle is one kernel (restart
+up to 112 here, past a few steps) make the two passes of ortho = 0 in it, held to
+the same bars; the one-reduction kernels themselves run at m = 128 and with the
+fp32 polynomial, and in test_gpu_general_kernels.py (preconditioners, separate
+reduction, every column-count class) and test_gpu_lowsync_large.py (fused, every
+class)."""
 import numpy as np
 import pytest
 
@@ -48,7 +49,7 @@ def _first(ref):
     return ref.cycle_starts[1] if len(ref.cycle_starts) > 1 else len(ref.hist)
 
 
-@pytest.mark.parametrize("side", [37, 64, 259])  # 1369 and 4096 rows (separate reduction), 67081 (fused)
+@pytest.mark.parametrize("side", [37, 64, 259])  # 1369, 4096 and 67081 rows
 def test_fp64_matches_oracle(side):
     A, bb = _system(side)
     M = B.Matrix.from_csr(A)
@@ -91,8 +92,8 @@ def test_gmres_ir_fp32_matches_oracle(side):
 @pytest.mark.parametrize("m", [1, 7, 16, 17, 33, 64, 65, 100, 128])
 @pytest.mark.parametrize("side", [37, 259])
 def test_restart_classes_first_cycle(m, side):
-    """Every column-count class of the fused and separate reduction kernels:
-    the first cycle against the oracle's (paper mode, full cycles)."""
+    """Every column-count class: the first cycle against the oracle's (paper
+    mode, full cycles)."""
     A, bb = _system(side, pe=20.0, seed=m)
     M = B.Matrix.from_csr(A)
     b = dev_tensor(bb)
@@ -132,7 +133,7 @@ def test_paper_mode_and_breakdown():
     M.close()
 
 
-@pytest.mark.parametrize("side", [14, 42])  # 3D: 2744 rows (separate reduction), 74088 rows (fused)
+@pytest.mark.parametrize("side", [14, 42])  # 3D: 2744 and 74088 rows
 def test_polynomial_preconditioned(side):
     A = P.conv_diff(3, side, 10.0, (1, 1, 1), (1, 1, 1e-2))
     bb = A.scipy() @ np.random.default_rng(0).uniform(-1, 1, A.n)

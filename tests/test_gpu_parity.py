@@ -349,10 +349,10 @@ def test_deterministic(conv64):
 
 
 def test_graph_replay_matches_direct_launches(conv64):
-    """Systems up to 2^18 rows run their cycles as a recorded HIP graph,
-    replayed once per refinement with eager kernels (residual, cast, host
-    read) in between; profiling switches to direct launches.  Both give the
-    same bits on every refinement (fp32 inner, fp64 inner, bf16 basis, a
+    """This system's cycles run as one kernel each, with eager kernels (residual,
+    cast, host read) in between; profiling launches its phases directly (graph
+    replay: test_gpu_general_kernels.py).  Both give the same bits on every
+    refinement (fp32 inner, fp64 inner, bf16 basis, a
     multi-cycle inner cap, and two solves in a row)."""
     s, M = conv64
     b = dev_tensor(s.b)

@@ -4,9 +4,10 @@ The cycle kernel (one cooperative launch, blocks exchanging their sums inside
 it) and its phases launched one by one (profile = 1) do the same operations in
 the same order, so their solutions and histories agree bit for bit; the
 phases read the basis and the vector from memory and have no exchange to get
-wrong.  Sizes sit at the edges of the slices, the blocks, the rows per lane
-(64 RL rows a block, RL = 1, 2, 3, 4, 6, 8, 12, 16) and the largest system of
-the path; both are held to the oracle's first cycle at the parity bars."""
+wrong.  Sizes sit at the edges of the slices and the blocks, in the ranges
+of several numbers of rows per lane (the edges of those:
+test_gpu_small_partitions.py) and at the largest system of the path; both are
+held to the oracle's first cycle at the parity bars."""
 import threading
 
 import numpy as np
@@ -78,8 +79,8 @@ def test_sizes(n, inner, basis):
     both(banded(n, (-33, -1, 0, 1, 33), n), 20, inner, basis, 45)
 
 
-# restart length (4, 8 or 16 columns a wave), rows up to which each number of
-# rows per lane is used: 128 blocks in fp32, 64 in fp64, 256 with the last
+# restart length (4, 8 or 16 columns a wave) and rows: 4, 8, 12 and 16 rows a lane
+# in fp32, 4 to 16 in fp64, up to the most of each restart length
 @pytest.mark.parametrize("inner,m,n", [
     ("fp32", 28, 128 * 192), ("fp32", 28, 128 * 768 + 1), ("fp32", 29, 128 * 256 + 1), ("fp32", 56, 128 * 512),
     ("fp32", 50, 128 * 1024 + 63), ("fp32", 50, 262144), ("fp32", 57, 128 * 128 + 1), ("fp32", 112, 131072),

@@ -1,10 +1,10 @@
 """gmresir_solve_noalloc (workspace from the library's static device array)
 against gmresir_solve with a caller workspace, through the C ABI.
 
-Both run the same kernels on the same workspace layout (the workspace is
-carved at the same offsets from a 256-byte aligned base; gmresir_solve
-replays small systems' cycles as a HIP graph, which gives the same bits as
-the direct launches the allocation-free call makes), so the bar is bitwise
+Both work on the same workspace layout (the workspace is carved at the same
+offsets from a 256-byte aligned base; gmresir_solve runs small systems' cycles
+as one kernel each, which gives the same bits as the phases that the
+allocation-free call launches), so the bar is bitwise
 equality of the solution, the iteration counts and the history.  Each case
 makes two calls in a row, the second on a smaller system, since every call
 on a GPU shares the one array and must not depend on what the last call left
