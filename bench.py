@@ -308,7 +308,16 @@ def main():
             "launches": nl, "measured_copy_GBps": copy_gbps, "measured_triad_GBps": triad_gbps,
             "bytes_model": "SpMV (4 + 4) nnz + 4 (N + 1) + 2*4 N (x read, w written; 4-byte column indices) + "
                            "4 N per basis column read or written (first CGS2 projection fused)",
+            "kernels": "launched one by one (profile = 1), as the breakdown's",
         }
+        # the timed solve makes a cycle of this system in one kernel
+        cycle = measured_traffic("mid_cycle") if traffic is not None else None
+        if cycle is not None:
+            out["roofline"]["timed_cycle_kernel"] = {
+                "kernel": "k_mid_cycle", "traffic_bytes_per_iteration": cycle / m,
+                "us_per_iteration_of_the_solve": t_ir / head["iters"] * 1e6,
+                "traffic_GBps_over_the_solve": cycle / m * head["iters"] / t_ir / 1e9,
+            }
         out["breakdown"] = {
             c: {"s": d_prof["cat_time_s"][c], "GBps": (d_prof["cat_bytes"][c] / d_prof["cat_time_s"][c] / 1e9
                                                       if d_prof["cat_time_s"][c] > 0 else 0.0),
