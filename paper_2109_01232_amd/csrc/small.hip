@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "exchange.hpp"
 #include "spmv.hpp"
@@ -178,28 +179,36 @@ __device__ __forceinline__ bool collect(const Wait& wt, word_t* words, int P, in
                                   sum))
       return false;
   } else {
-    for (int b0 = 0; b0 < P; b0 += NB * G) {
-      word_t w[G][WV];
+    // GN loads of NB blocks each from block b0; past the last block its line
+    // again: a load under a condition has its result copied, and waited for, before
+    // the next goes out (fp64, 15625 rows, 36.1 instead of 28.7 us an iteration)
+    auto pass = [&](auto gn, int b0) {
+      constexpr int GN = decltype(gn)::value;
+      word_t w[GN][WV];
       const bool ok = wait_for<ALONE>(wt, [&] {
         bool right = true;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
+        for (int g = 0; g < GN; ++g) {
           const int b = b0 + NB * g + bl;
-          if (NB * g + b0 < P)
 #pragma unroll
-            for (int h = 0; h < WV; ++h) w[g][h] = look_at<ALONE>(p + (unsigned)((b < P ? b : P - 1) * LINE * WV + h));
+          for (int h = 0; h < WV; ++h) w[g][h] = look_at<ALONE>(p + (unsigned)((b < P ? b : P - 1) * LINE * WV + h));
         }
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-          if (NB * g + b0 < P)
+        for (int g = 0; g < GN; ++g)
 #pragma unroll
-            for (int h = 0; h < WV; ++h) right = right && ((unsigned int)w[g][h] == tag || q >= nq);
+          for (int h = 0; h < WV; ++h) right = right && ((unsigned int)w[g][h] == tag || q >= nq);
         return right;
       });
-      if (!ok) return false;
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-        if (NB * g + b0 < P && NB * g + b0 + bl < P && q < nq) sum += word_value(w[g], T(0));
+      for (int g = 0; g < GN; ++g)
+        if (NB * g + b0 + bl < P && q < nq) sum += word_value(w[g], T(0));
+      return ok;
+    };
+    if (WV == 1 && P <= NB * G / 4) {  // (fp64: the second copy of the code costs what it gives)
+      if (!pass(std::integral_constant<int, G / 4>{}, 0)) return false;
+    } else {
+      for (int b0 = 0; b0 < P; b0 += NB * G)
+        if (!pass(std::integral_constant<int, G>{}, b0)) return false;
     }
     sum = lane_sum<W>(sum);
   }
