@@ -1789,7 +1789,9 @@ int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const i
   S.col = colidx;
   S.vals = vals;
   S.ns = (int)ns;
-  S.nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(SETUP_MAX_BLOCKS, ns / SETUP_MIN_SLICES));
+  // a slice a wave; with fewer slices than would fill the CUs so, a slice a block
+  // (a dense matrix of 300 rows 472 -> 242 us, 30 x 30 x 30 27-point 100 -> 107)
+  S.nblocks = (int)std::min<int64_t>(ns, std::max<int64_t>(SETUP_MIN_BLOCKS, std::min<int64_t>(SETUP_MAX_BLOCKS, ns / NWAVES)));
   S.nseg = (int)((n + (int64_t)TILE_SEG * TILE_UNIT - 1) / ((int64_t)TILE_SEG * TILE_UNIT));
   // a wave stages a slice with up to one entry a row more than the average
   S.cap = (int)std::max<int64_t>(256, std::min<int64_t>(2048, SELL_C * (nnz / n + 2)));
@@ -1810,24 +1812,39 @@ int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const i
   S.scol = (int*)(tend + align_up((ns + 1) * 4));
   S.sv32 = (float*)((char*)S.scol + align_up(E * 4));
   S.sv64 = (double*)((char*)S.sv32 + align_up(E * 4));
-  const size_t seg_lds = (size_t)(TILE_SEG + TILE_SPAN + 1) * sizeof(int);
-  const size_t scan_lds = std::max(seg_lds, (size_t)NWAVES * (S.cap + UNION_SLOTS) * sizeof(int));
-  const size_t build_lds = std::max(seg_lds, (size_t)NWAVES * S.cap * (sizeof(int) + sizeof(double)));
-  hipLaunchKernelGGL(k_setup_scan, dim3(S.nblocks + (S.nseg > 1 ? S.nseg : 0)), dim3(BLOCK), scan_lds, s, S);
-  hipLaunchKernelGGL(k_setup_decide, dim3(1), dim3(SETUP_MAX_BLOCKS), 0, s, S);
-  // a matrix without slices has its values' fp32 copy made by four loads a thread
-  const int extra = std::max<int>(0, (int)std::min<int64_t>(SETUP_MAX_BLOCKS, nnz / (4 * BLOCK)) - S.nblocks);
-  hipLaunchKernelGGL(k_setup_build, dim3(S.nblocks + S.nseg + extra), dim3(BLOCK), build_lds, s, S);
-  HIP_TRY(hipGetLastError());
   SetupDecision dec;
-  // rows this long are cut into tiles on the host: their pointers come along
   std::vector<int32_t> rp;
-  if (nnz > n * (TILE_MAX_ROW / 2)) {
+  if (nnz > n * SELL_MAX_ROW) {
+    // some row is too long for slices and for tiles of whole units: the values'
+    // fp32 copy is all that is left to the GPU (20000 rows of 583 entries: the
+    // set-up kernels 583 us, this 81)
+    hipLaunchKernelGGL(k_setup_values, dim3((unsigned)std::min<int64_t>(4 * SETUP_MAX_BLOCKS, nnz / (4 * BLOCK) + 1)),
+                       dim3(BLOCK), 0, s, S);
+    HIP_TRY(hipGetLastError());
     rp.resize(n + 1);
     HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    dec = SetupDecision{rp[0], rp[n], INT32_MAX, INT32_MAX};
+    for (int64_t r = n - 1; r >= 0; --r)
+      if (rp[r + 1] < rp[r]) dec.bad_row = (int32_t)r;
+  } else {
+    const size_t seg_lds = (size_t)(TILE_SEG + TILE_SPAN + 1) * sizeof(int);
+    const size_t scan_lds = std::max(seg_lds, (size_t)NWAVES * (S.cap + UNION_SLOTS) * sizeof(int));
+    const size_t build_lds = std::max(seg_lds, (size_t)NWAVES * S.cap * (sizeof(int) + sizeof(double)));
+    hipLaunchKernelGGL(k_setup_scan, dim3(S.nblocks + (S.nseg > 1 ? S.nseg : 0)), dim3(BLOCK), scan_lds, s, S);
+    hipLaunchKernelGGL(k_setup_decide, dim3(1), dim3(SETUP_MAX_BLOCKS), 0, s, S);
+    // a matrix without slices has its values' fp32 copy made by four loads a thread
+    const int extra = std::max<int>(0, (int)std::min<int64_t>(SETUP_MAX_BLOCKS, nnz / (4 * BLOCK)) - S.nblocks);
+    hipLaunchKernelGGL(k_setup_build, dim3(S.nblocks + S.nseg + extra), dim3(BLOCK), build_lds, s, S);
+    HIP_TRY(hipGetLastError());
+    // rows this long are cut into tiles on the host: their pointers come along
+    if (nnz > n * (TILE_MAX_ROW / 2)) {
+      rp.resize(n + 1);
+      HIP_TRY(hipMemcpyAsync(rp.data(), rowptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    }
+    HIP_TRY(hipMemcpyAsync(&dec, S.dec, sizeof(dec), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
   }
-  HIP_TRY(hipMemcpyAsync(&dec, S.dec, sizeof(dec), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
   if (dec.first != 0 || dec.last != nnz) {
     set_error("gmresir_matrix_create: rowptr[0] must be 0 and rowptr[n] == nnz");
     return GMRESIR_ERR_INVALID_ARG;

@@ -1,7 +1,8 @@
 // Matrix set-up on the GPU (gfx950): the row-tile table, the choice of the
 // SpMV layout and the sliced copies, from the caller's CSR arrays.
 //
-// Three launches and one read of a 64-byte decision by the host:
+// Three launches and one read of a 64-byte decision by the host (rows of more than
+// SELL_MAX_ROW entries on average: one, k_setup_values, and the row pointers read):
 //   k_setup_scan    per 64-row slice: longest row, size of the sorted union
 //                   of its rows' column offsets, order and distance checks;
 //                   per tile segment: where a tile chain entering it leaves it
@@ -12,7 +13,7 @@
 //
 // Bound by memory: the CSR arrays are read once (the column indices twice) and
 // every copy is written once.  7-point 150^3 (23.5 M nonzeros), set-up and
-// one product in each precision: 0.39 ms (scan 70 us, decide 30, build 190),
+// one product in each precision: 0.34 ms (scan 76 us, decide 30, build 135),
 // where copying the row pointers and column indices to the host and walking them
 // there took 38.0 ms.
 #pragma once
@@ -22,7 +23,7 @@
 namespace gir {
 
 constexpr int SETUP_MAX_BLOCKS = 1024;  // = threads of k_setup_decide
-constexpr int SETUP_MIN_SLICES = NWAVES;  // slices per block at least: one a wave
+constexpr int SETUP_MIN_BLOCKS = 256;   // where there are as many slices
 constexpr int SETUP_CHUNK = 256;        // slices whose pointers a block scans at once
 // Tiles start on multiples of 8 rows ("units") as long as 8 rows fit a tile,
 // i.e. no row is longer than TILE_NNZ / 8; longer rows go through the host.
@@ -164,15 +165,25 @@ __device__ __forceinline__ void tile_chains(const Setup& S, int seg, int* cum) {
   if (threadIdx.x >= TILE_SPAN) return;
   const long long left = ((long long)S.n + TILE_UNIT - 1) / TILE_UNIT - (long long)seg * TILE_SEG;
   const int nu = left < TILE_SEG + TILE_SPAN ? (int)left : TILE_SEG + TILE_SPAN;  // last boundary, in units
-  int u = threadIdx.x, tiles = 0;
-  while (u < TILE_SEG && u < nu) {
-    // the last boundary of a tile from u: at most TILE_SPAN units, TILE_NNZ nonzeros
+  // a unit that fills more than a tile has a row too long for units: the host cuts
+  bool fits = true;
+  for (int i = threadIdx.x; i < nu; i += TILE_SPAN) fits = fits && cum[i + 1] - cum[i] <= TILE_NNZ;
+  fits = __all(fits);
+  int u = threadIdx.x, tiles = 0, span = TILE_SPAN / 2;
+  while (fits && u < TILE_SEG && u < nu) {
+    // the last boundary of a tile from u: at most TILE_SPAN units, TILE_NNZ
+    // nonzeros; looked for first where the tile before had its own
     int lo = u + 1, hi = min(u + TILE_SPAN, nu);
+    const int guess = min(u + span, hi);
+    if (cum[guess] - cum[u] > TILE_NNZ) hi = guess - 1;
+    else lo = guess;
+    if (lo < hi && cum[lo + 1] - cum[u] > TILE_NNZ) hi = lo;
     while (lo < hi) {
       const int mid = (lo + hi + 1) / 2;
       if (cum[mid] - cum[u] <= TILE_NNZ) lo = mid;
       else hi = mid - 1;
     }
+    span = lo - u;
     u = lo;
     ++tiles;
   }
@@ -209,21 +220,21 @@ __global__ __launch_bounds__(BLOCK) void k_setup_scan(Setup S) {
     max_len = max(max_len, K);
     int U = 0;
     if (K > SELL_MAX_ROW) flags |= SETUP_LONG;
-    if (ok && K > 0 && K <= SELL_MAX_ROW) {
+    // (past the storage the matrix has no slices and its union is not asked for)
+    if (ok && K > 0 && K <= SELL_MAX_ROW && SELL_C * (sumK + K) <= S.max_entries) {
       const int rows = min(SELL_C, S.n - s * SELL_C);
       const int q0 = __builtin_amdgcn_readlane(p0, 0);
       const int cnt = __builtin_amdgcn_readlane(p1, rows - 1) - q0;
       const int a = r < S.n ? p0 - q0 : 0, b = r < S.n ? p1 - q0 : 0;
       // Each lane walks its row beside the longest one's.  Rows that all begin
       // as that one does (the inside of a stencil's grid) have its offsets for
-      // their union.  Others' are merged, smallest offset by smallest offset:
-      // quick where the lanes share most of them (a grid's edge), else as many
-      // steps as there are entries, so past twice the longest row's the union is
-      // counted in the table (1000 random rows of 20 entries, whole set-up, 703
-      // -> 78 us; 300000 836 -> 214).  Slices too large to stage are not
-      // merged, each step would read memory.
+      // their union.  Where few do not (a grid's edge) the rows are merged,
+      // smallest offset by smallest offset; else that takes as many steps as there
+      // are entries, and the union is counted in the table (1000 random rows of 20
+      // entries, whole set-up, 703 -> 55 us; 300000 836 -> 150).  Slices
+      // too large to stage are not merged, each step would read memory.
       auto look = [&](const int* cols, bool staged) {
-        constexpr int AHEAD = 4;  // entries loaded together
+        constexpr int AHEAD = 8;  // entries loaded together
         const int longest = __ffsll(__ballot(len == K)) - 1;
         bool unordered = false, far = false, differ = false;
         int prev = 0;
@@ -250,7 +261,8 @@ __global__ __launch_bounds__(BLOCK) void k_setup_scan(Setup S) {
         }
         U = K;
         if (!__any(differ)) return;
-        if (staged) {
+        const bool merge = staged && __popcll(__ballot(differ)) <= WAVE / 4;
+        if (merge) {
           SliceCursor cu;
           cu.start(cols, r, a, b);
           int m, at;
@@ -258,7 +270,7 @@ __global__ __launch_bounds__(BLOCK) void k_setup_scan(Setup S) {
           for (U = 0; U <= 2 * K; ++U)
             if (!cu.next(m, hit, at)) break;
         }
-        if (!staged || U > 2 * K) {
+        if (!merge || U > 2 * K) {
           for (int i = lane; i < UNION_SLOTS; i += WAVE) table[i] = INT32_MIN;
           wave_lds_sync();
           U = 0;
@@ -429,6 +441,20 @@ __device__ __forceinline__ void tile_emit(const Setup& S, int seg, int* cum) {
   }
 }
 
+// The fp32 copy of the CSR values by block `block` of `blocks`.
+__device__ __forceinline__ void cast_values(const Setup& S, int block, int blocks) {
+  const long long stride = (long long)blocks * BLOCK;
+  for (long long i = (long long)block * BLOCK + threadIdx.x; i < S.nnz; i += 4 * stride) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = S.vals[i + u * stride < S.nnz ? i + u * stride : i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i + u * stride < S.nnz) S.v32[i + u * stride] = (float)v[u];
+  }
+}
+__global__ __launch_bounds__(BLOCK) void k_setup_values(Setup S) { cast_values(S, blockIdx.x, gridDim.x); }
+
 __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
   const SetupDecision* dec = S.dec;
   if (dec->bad_row != INT32_MAX || dec->first != 0 || dec->last != S.nnz) return;
@@ -441,17 +467,8 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
   }
   if (!sell) {
     // no slices to fill: the values alone, over as many blocks as they need
-    // (slice by slice, 3000 rows of 550 entries, 750 us)
-    const long long stride = (long long)(gridDim.x - S.nseg) * BLOCK;
-    for (long long i = (long long)(extra < 0 ? (int)blockIdx.x : S.nblocks + extra) * BLOCK + threadIdx.x; i < S.nnz;
-         i += 4 * stride) {
-      double v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = S.vals[i + u * stride < S.nnz ? i + u * stride : i];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i + u * stride < S.nnz) S.v32[i + u * stride] = (float)v[u];
-    }
+    // (slice by slice, 3000 rows of 550 entries, which k_setup_values now takes, 750 us)
+    cast_values(S, extra < 0 ? (int)blockIdx.x : S.nblocks + extra, gridDim.x - S.nseg);
     return;
   }
   if (extra >= 0) return;
@@ -494,13 +511,25 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
       const int q0 = __builtin_amdgcn_readlane(p0, 0);
       const int cnt = __builtin_amdgcn_readlane(p1, rows - 1) - q0;
       const bool staged = cnt <= S.cap;
-      for (int i = lane; i < cnt; i += WAVE) {
-        const double v = S.vals[q0 + i];
-        S.v32[q0 + i] = (float)v;
-        if (staged) {
-          sv[i] = v;
-          sc[i] = S.col[q0 + i];
+      // (four entries' loads together: 7-point 150^3, this kernel 190 -> 135 us)
+      for (int i = lane; i < cnt; i += 4 * WAVE) {
+        double v[4];
+        int c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int at = q0 + min(i + u * WAVE, cnt - 1);
+          v[u] = S.vals[at];
+          if (staged) c[u] = S.col[at];
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (i + u * WAVE < cnt) {
+            S.v32[q0 + i + u * WAVE] = (float)v[u];
+            if (staged) {
+              sv[i + u * WAVE] = v[u];
+              sc[i + u * WAVE] = c[u];
+            }
+          }
       }
       const int a = r < S.n ? p0 - q0 : 0, b = r < S.n ? p1 - q0 : 0;
       const int base = s_base[s - c0];
@@ -522,15 +551,29 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
         } else {
           // columns, or (d16) 16-bit offsets from the row; padding entries
           // point at the row itself (offset 0), rows past n at row 0
+          // (four entries' loads go out before their stores)
           const int rr = r < S.n ? r : 0;
-          for (int k = 0; k < K; ++k, e += SELL_C) {
-            const bool in = a + k < b;
-            const int c = in ? cols[a + k] : rr;
-            const double v = in ? vals[a + k] : 0.0;
-            if (d16) ((short*)S.scol)[e] = (short)(c - rr);
-            else S.scol[e] = c;
-            S.sv64[e] = v;
-            S.sv32[e] = (float)v;
+          for (int k0 = 0; k0 < K; k0 += 4) {
+            int c[4];
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int p = min(a + k0 + u, cnt - 1);
+              c[u] = cols[p];
+              v[u] = vals[p];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (k0 + u < K) {
+                const bool in = a + k0 + u < b;
+                const int col = in ? c[u] : rr;
+                const double val = in ? v[u] : 0.0;
+                if (d16) ((short*)S.scol)[e] = (short)(col - rr);
+                else S.scol[e] = col;
+                S.sv64[e] = val;
+                S.sv32[e] = (float)val;
+                e += SELL_C;
+              }
           }
         }
       };
