@@ -1816,7 +1816,7 @@ int gmresir_matrix_create(int64_t n, int64_t nnz, const int32_t* rowptr, const i
   std::vector<int32_t> rp;
   if (nnz > n * SELL_MAX_ROW) {
     // some row is too long for slices and for tiles of whole units: the values'
-    // fp32 copy is all that is left to the GPU (20000 rows of 583 entries: the
+    // fp32 copy is all that is left to the GPU (20000 rows of 591 entries: the
     // set-up kernels 583 us, this 81)
     hipLaunchKernelGGL(k_setup_values, dim3((unsigned)std::min<int64_t>(4 * SETUP_MAX_BLOCKS, nnz / (4 * BLOCK) + 1)),
                        dim3(BLOCK), 0, s, S);

@@ -467,7 +467,7 @@ __global__ __launch_bounds__(BLOCK) void k_setup_build(Setup S) {
   }
   if (!sell) {
     // no slices to fill: the values alone, over as many blocks as they need
-    // (slice by slice, 3000 rows of 550 entries, which k_setup_values now takes, 750 us)
+    // (slice by slice, 3000 rows of 544 entries, which k_setup_values now takes, 750 us)
     cast_values(S, extra < 0 ? (int)blockIdx.x : S.nblocks + extra, gridDim.x - S.nseg);
     return;
   }
